@@ -6,8 +6,8 @@
 // N_G rounded up to 64).  For the block K of columns/rows:
 //   D^-1   the inverse of the diagonal block A[K,K]: a copy of the block
 //          inverted by the same elimination 64 columns at a time, whose
-//          64 x 64 pivot blocks are inverted by one workgroup in LDS (scalar
-//          Gauss-Jordan);
+//          64 x 64 pivot blocks are inverted by one workgroup in registers
+//          (scalar Gauss-Jordan);
 //   L      = A[:, K] with its K rows zeroed (saved), then A[not K, K] = 0;
 //   R      = D^-1 A[K, :], with R[:, K] = D^-1, written back as A[K, :];
 //   A     -= L R  (one GEMM of N_G x 512 x N_G on FP64 MFMA: 64 flops per
@@ -28,7 +28,7 @@
 namespace gw {
 namespace {
 
-constexpr int kB = 64;   // width of the pivot blocks inverted in LDS
+constexpr int kB = 64;   // width of the pivot blocks inverted by one workgroup
 constexpr int kW = 512;  // width of the elimination's blocks
 
 // out[w] = I - diag(v) chi[w]
@@ -49,48 +49,77 @@ __global__ __launch_bounds__(256) void build_eps_kernel(const double2* __restric
 // batch at a + w * sa.
 
 // d[w] = A[w][K,K]^-1 for the bk x bk block at (k0, k0) (bk <= 64): scalar
-// Gauss-Jordan in LDS, no pivoting; d[w] at d + w * kB * kB, leading dimension kB.
+// Gauss-Jordan, no pivoting; d[w] at d + w * kB * kB, leading dimension kB.
+//
+// A chain of bk dependent steps on one workgroup, so the latency of a step is
+// the whole cost.  The block lives in registers (thread (ti, tj) holds rows
+// ti + 16 r and columns tj + 16 c); a step passes only the pivot row and
+// column through LDS, in two buffers, so it costs one barrier, one round of
+// LDS reads and one division.  Holding the block in LDS took four barriers and
+// three passes over it per step: 182 us for a 64 x 64 block against 42 us.
 __global__ __launch_bounds__(256) void block_inverse_kernel(const double2* __restrict__ a, int n,
                                                             int64_t sa, int k0, int bk,
                                                             double2* __restrict__ d) {
-    __shared__ double2 s[kB][kB + 1];
+    constexpr int R = kB / 16;
+    __shared__ double2 s_row[2][kB], s_col[2][kB];
     const int64_t w = blockIdx.x;
     const double2* aw = a + w * sa;
-    for (int e = threadIdx.x; e < bk * bk; e += 256) {
-        const int i = e / bk, j = e % bk;
-        s[i][j] = aw[static_cast<int64_t>(k0 + i) * n + k0 + j];
-    }
-    __syncthreads();
-    for (int p = 0; p < bk; ++p) {
-        const double2 piv = s[p][p];
-        const double den = piv.x * piv.x + piv.y * piv.y;
-        const double2 inv = make_double2(piv.x / den, -piv.y / den);
-        __syncthreads();
-        // row p scaled (its pivot becomes 1/pivot)
-        for (int j = threadIdx.x; j < bk; j += 256)
-            s[p][j] = j == p ? inv : cmul(inv, s[p][j]);
-        __syncthreads();
-        // other rows: a_ij -= a_ip a_pj (j != p), a_ip = -a_ip / pivot
-        for (int e = threadIdx.x; e < bk * bk; e += 256) {
-            const int i = e / bk, j = e % bk;
-            if (i == p) continue;
-            const double2 aip = s[i][p];
-            if (j == p) continue;
-            const double2 pr = cmul(aip, s[p][j]);
-            s[i][j] = make_double2(s[i][j].x - pr.x, s[i][j].y - pr.y);
+    const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
+    double2 x[R][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            const int i = ti + 16 * r, j = tj + 16 * c;
+            x[r][c] = i < bk && j < bk ? aw[static_cast<int64_t>(k0 + i) * n + k0 + j]
+                                       : make_double2(0.0, 0.0);
         }
-        __syncthreads();
-        for (int i = threadIdx.x; i < bk; i += 256)
-            if (i != p) {
-                const double2 m = cmul(s[i][p], inv);
-                s[i][p] = make_double2(-m.x, -m.y);
+#pragma unroll
+    for (int pr = 0; pr < R; ++pr) {
+        for (int pt = 0; pt < 16; ++pt) {
+            const int p = 16 * pr + pt, buf = p & 1;
+            if (p >= bk) break;
+            if (tj == pt)
+#pragma unroll
+                for (int r = 0; r < R; ++r) s_col[buf][ti + 16 * r] = x[r][pr];
+            if (ti == pt)
+#pragma unroll
+                for (int c = 0; c < R; ++c) s_row[buf][tj + 16 * c] = x[pr][c];
+            __syncthreads();
+            const double2 piv = s_row[buf][p];
+            const double den = piv.x * piv.x + piv.y * piv.y;
+            const double2 inv = make_double2(piv.x / den, -piv.y / den);
+            // row p scaled, its pivot 1 / pivot; a_ij -= a_ip a_pj for the other
+            // rows (column p: 0 - a_ip / pivot)
+            double2 row[R];
+#pragma unroll
+            for (int c = 0; c < R; ++c) row[c] = cmul(inv, s_row[buf][tj + 16 * c]);
+            if (tj == pt) {
+                row[pr] = inv;
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[r][pr] = make_double2(0.0, 0.0);
             }
-        __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double2 col = s_col[buf][ti + 16 * r];
+#pragma unroll
+                for (int c = 0; c < R; ++c) {
+                    const double2 v = cmul(col, row[c]);
+                    x[r][c] = make_double2(x[r][c].x - v.x, x[r][c].y - v.y);
+                }
+            }
+            if (ti == pt)
+#pragma unroll
+                for (int c = 0; c < R; ++c) x[pr][c] = row[c];
+        }
     }
-    for (int e = threadIdx.x; e < bk * bk; e += 256) {
-        const int i = e / bk, j = e % bk;
-        d[w * kB * kB + i * kB + j] = s[i][j];
-    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            const int i = ti + 16 * r, j = tj + 16 * c;
+            if (i < bk && j < bk) d[w * kB * kB + i * kB + j] = x[r][c];
+        }
 }
 
 // L[w] = A[w][:, K] (rows in K zeroed), then A[w][i, K] = 0 for rows i not in
@@ -150,8 +179,8 @@ size_t level_bytes(int n, int nz, int kb) {
 }
 
 // In-place Gauss-Jordan inversion of nz matrices (n x n, batch stride sa),
-// blocks of width kb: 64 (pivot blocks inverted in LDS) or more (pivot blocks
-// copied and inverted by this routine at width 64).
+// blocks of width kb: 64 (pivot blocks inverted by one workgroup) or more
+// (pivot blocks copied and inverted by this routine at width 64).
 void gj_invert(double2* a, int n, int64_t sa, int nz, int kb, char* ws, hipStream_t s) {
     double2* d = reinterpret_cast<double2*>(ws);
     double2* l = reinterpret_cast<double2*>(ws + al256(static_cast<size_t>(nz) * kb * kb * 16));
