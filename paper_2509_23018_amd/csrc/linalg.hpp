@@ -61,7 +61,7 @@ size_t jacobi_work_bytes(int n, int batch);
 
 // Inverse of the upper Cholesky factor of an n x n Hermitian positive
 // semidefinite G (row-major): G = R^H R, rinv = R^-1 (upper triangular,
-// n x n), blocked by 64 (the diagonal blocks factored and inverted in LDS, the
+// n x n), blocked by 64 (the diagonal blocks by one workgroup each, the
 // panels and trailing updates as GEMMs).  A pivot at or below 1e-26 of G's
 // largest diagonal entry marks its direction as lost: that row of R and that
 // row and column of rinv are zero, so Y rinv has a zero column there.  G is

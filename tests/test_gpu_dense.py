@@ -35,3 +35,25 @@ def test_epsinv_pivot_blocks(n):
     cond = max(np.linalg.cond(w) for w in want)
     for w in range(2):
         assert rel_fro(got[w], want[w]) < 8 * EPS * cond * np.sqrt(n + 1)
+
+
+# Cholesky blocks of 64 on nb = n_eig + guard columns: below, at and past one
+# and two blocks; rank: of the matrix (below nb: directions are lost)
+@pytest.mark.parametrize("n_eig,guard,rank", [(40, 23, 200), (40, 24, 200), (41, 24, 200),
+                                              (100, 28, 200), (100, 29, 200), (30, 40, 50)])
+def test_diag_cholesky_blocks(n_eig, guard, rank):
+    ng = 200
+    rng = np.random.default_rng(n_eig + guard)
+    q = np.linalg.qr(_crand(rng, ng, ng))[0]
+    ev = np.zeros(ng)
+    ev[:rank] = 0.95 ** np.arange(rank)              # -chi, decreasing
+    chi = -(q * ev) @ q.conj().T
+    chi = 0.5 * (chi + chi.conj().T)
+    basis, w, info = gw.gw_subspace_basis(_to(chi), n_eig, guard=guard, max_iter=200)
+    basis, w = basis.cpu().numpy(), w.cpu().numpy()
+    # the default tol bounds each kept pair's residual by 1e-10 of the Gershgorin bound
+    res = 1e-10 * info["bound"]
+    assert info["residual"] <= 1e-10
+    assert np.abs(w + ev[:n_eig]).max() < res
+    assert np.abs(basis.conj().T @ basis - np.eye(n_eig)).max() < 1e-13
+    assert np.linalg.norm(chi @ basis - basis * w, axis=0).max() < 1.01 * res
