@@ -13,150 +13,225 @@ namespace {
 
 // ---------------------------------------------------------------- GEMM
 //
-// One workgroup of 4 waves per 64 x 64 tile of C; each wave owns a 32 x 32
-// quarter as 2 x 2 blocks of the 16x16x4 FP64 MFMA.  The k dimension is
-// staged through LDS 16 at a time; the next stage's global loads are issued
-// into registers before the current stage's MFMAs (loads unconditional on
-// clamped addresses, masks and conjugation applied at the LDS write).  Each
-// complex multiply-add takes three real products (p1 = ar br, p2 = ai bi,
-// p3 = (ar + ai)(br + bi); Re = p1 - p2, Im = p3 - p1 - p2).
+// One workgroup of 4 waves (2 x 2) per 32 BX x 32 tile of C; each wave owns BX
+// blocks of the 16x16x4 FP64 MFMA.  The k dimension is staged through LDS 16
+// at a time, in two buffers: stage t + 2 is loaded into registers while stage
+// t is multiplied, and written to LDS a stage before its use, one barrier per
+// stage.  Rows and columns past the edge of C are clamped: they feed only
+// entries that are not stored.  Only the last, partial stage masks its k.
+// Each complex multiply-add takes three real products (p1 = ar br, p2 = ai bi,
+// p3 = (ar + ai)(br + bi); Re = p1 - p2, Im = p3 - p1 - p2).  Every entry of C
+// is summed in the same order whatever the tile, so the tile does not change a
+// bit of the result.
+//
+// Bound by the FP64 matrix pipe where the grid fills the chip, by the chain of
+// stages where it does not.  Measured against 64 x 64 tiles of one LDS buffer,
+// loads one stage ahead and clamps and masks in every stage (TFLOP/s count the
+// six flops executed per complex multiply-add):
+//   2048 x 2048 x 2048        960 ->  774 us (53.7 -> 66.6 TFLOP/s), BX = 2
+//   4 of 2007 x 2007 x 512    914 ->  805 us (54.2 -> 61.5)
+//   3840 x 603 x 6031        2630 -> 1516 us (31.9 -> 55.3)
+//   3840 x 400 x 2007         445 ->  359 us (41.6 -> 51.5), BX = 1
+//   1189 x 135 x 1189         154 ->   44 us,                BX = 1
+//   135 x 135 x 1189          158 ->   46 us,                BX = 1
+// Writing stage t + 1 to LDS before the MFMAs of stage t (915 us for the
+// first) and 32-deep stages (47 us for the fifth) were slower.
 
-template <int OPA, int OPB>
+template <int OPA, int OPB, int BX>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void zgemm_kernel(
     ZGemm g) {
-    __shared__ double2 s_a[64][17];  // [m][k]
-    __shared__ double2 s_b[16][65];  // [k][n]
+    constexpr int TM = 32 * BX, TN = 32, KT = 16, PD = 2;
+    constexpr int NA = TM * KT / 256, NB = TN * KT / 256;
+    __shared__ double2 s_a[2][TM][KT + 1];  // [m][k]
+    __shared__ double2 s_b[2][KT][TN + 1];  // [k][n]
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, row = lane & 15, kq = lane >> 4;
     const int wi = wave >> 1, wj = wave & 1;
     const int64_t bz = blockIdx.z;
-    const double2* A = g.a + bz * g.stride_a;
-    const double2* B = g.b + bz * g.stride_b;
-    double2* C = g.c + bz * g.stride_c;
-    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-    const int mlast = g.m - 1, nlast = g.n - 1, klast = g.k - 1;
+    const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
 
-    dbl4 p1[2][2], p2[2][2], p3[2][2];
+    dbl4 p1[BX], p2[BX], p3[BX];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) p1[x][y] = p2[x][y] = p3[x][y] = zero4();
+    for (int x = 0; x < BX; ++x) p1[x] = p2[x] = p3[x] = zero4();
 
-    double2 ra[4], rb[4];
-    auto fetch = [&](int k0) {
+    // staged element e = tid + 256 u: (m, k) of the A side, (k, n) of the B side
+    auto a_mk = [&](int u, int& mm, int& kk) {
+        const int e = tid + 256 * u;
+        mm = OPA == kOpN ? e / KT : e % TM;
+        kk = OPA == kOpN ? e % KT : e / TM;
+    };
+    auto b_kn = [&](int u, int& kk, int& nn) {
+        const int e = tid + 256 * u;
+        nn = OPB == kOpN ? e % TN : e / KT;
+        kk = OPB == kOpN ? e / TN : e % KT;
+    };
+    const double2 *pa[NA], *pb[NB];  // element u of the next stage to load
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = tid + 256 * u;
-            const double2* sa;
-            if (OPA == kOpN)
-                sa = A + static_cast<int64_t>(min(i0 + (e >> 4), mlast)) * g.lda +
-                     min(k0 + (e & 15), klast);
-            else
-                sa = A + static_cast<int64_t>(min(k0 + (e >> 6), klast)) * g.lda +
-                     min(i0 + (e & 63), mlast);
-            ra[u].x = sa->x;
-            ra[u].y = sa->y;
-            const double2* sb;
-            if (OPB == kOpN)
-                sb = B + static_cast<int64_t>(min(k0 + (e >> 6), klast)) * g.ldb +
-                     min(j0 + (e & 63), nlast);
-            else
-                sb = B + static_cast<int64_t>(min(j0 + (e >> 4), nlast)) * g.ldb +
-                     min(k0 + (e & 15), klast);
-            rb[u].x = sb->x;
-            rb[u].y = sb->y;
+    for (int u = 0; u < NA; ++u) {
+        int mm, kk;
+        a_mk(u, mm, kk);
+        const int64_t im = min(i0 + mm, g.m - 1);
+        pa[u] = g.a + bz * g.stride_a + (OPA == kOpN ? im * g.lda + kk : kk * g.lda + im);
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        int kk, nn;
+        b_kn(u, kk, nn);
+        const int64_t in = min(j0 + nn, g.n - 1);
+        pb[u] = g.b + bz * g.stride_b + (OPB == kOpN ? kk * g.ldb + in : in * g.ldb + kk);
+    }
+    const int64_t da = OPA == kOpN ? KT : KT * g.lda, db = OPB == kOpN ? KT * g.ldb : KT;
+    double2 ra[PD][NA], rb[PD][NB];
+    // component loads: a whole-struct copy would be fused with the LDS write
+    // into one copy behind the MFMAs
+    auto fetch = [&](int slot) {
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            ra[slot][u].x = pa[u]->x;
+            ra[slot][u].y = pa[u]->y;
+            pa[u] += da;
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            rb[slot][u].x = pb[u]->x;
+            rb[slot][u].y = pb[u]->y;
+            pb[u] += db;
         }
     };
-    if (g.k > 0) fetch(0);
-    for (int k0 = 0; k0 < g.k; k0 += 16) {
-        __syncthreads();  // every wave is done with the previous stage
+    const int nfull = g.k / KT, rem = g.k % KT;
+    auto fetch_rem = [&](int slot) {  // the last, partial stage: k past the end is zero
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = tid + 256 * u;
+        for (int u = 0; u < NA; ++u) {
             int mm, kk;
-            if (OPA == kOpN) {
-                mm = e >> 4;
-                kk = e & 15;
-            } else {
-                kk = e >> 6;
-                mm = e & 63;
-            }
-            const bool oka = i0 + mm < g.m && k0 + kk < g.k;
-            s_a[mm][kk] = oka ? make_double2(ra[u].x, OPA == kOpC ? -ra[u].y : ra[u].y)
-                              : make_double2(0.0, 0.0);
-            int nn;
-            if (OPB == kOpN) {
-                kk = e >> 6;
-                nn = e & 63;
-            } else {
-                nn = e >> 4;
-                kk = e & 15;
-            }
-            const bool okb = j0 + nn < g.n && k0 + kk < g.k;
-            s_b[kk][nn] = okb ? make_double2(rb[u].x, OPB == kOpC ? -rb[u].y : rb[u].y)
-                              : make_double2(0.0, 0.0);
+            a_mk(u, mm, kk);
+            ra[slot][u] = kk < rem ? *pa[u] : make_double2(0.0, 0.0);
         }
-        __syncthreads();
-        __builtin_amdgcn_s_setprio(1);
-        if (k0 + 16 < g.k) fetch(k0 + 16);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            double2 a[2], b[2];
-            double as[2], bs[2];
+        for (int u = 0; u < NB; ++u) {
+            int kk, nn;
+            b_kn(u, kk, nn);
+            rb[slot][u] = kk < rem ? *pb[u] : make_double2(0.0, 0.0);
+        }
+    };
+    auto store = [&](int slot, int buf) {
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                a[x] = s_a[wi * 32 + x * 16 + row][s * 4 + kq];
+        for (int u = 0; u < NA; ++u) {
+            int mm, kk;
+            a_mk(u, mm, kk);
+            s_a[buf][mm][kk] = make_double2(ra[slot][u].x, OPA == kOpC ? -ra[slot][u].y
+                                                                       : ra[slot][u].y);
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            int kk, nn;
+            b_kn(u, kk, nn);
+            s_b[buf][kk][nn] = make_double2(rb[slot][u].x, OPB == kOpC ? -rb[slot][u].y
+                                                                       : rb[slot][u].y);
+        }
+    };
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int s = 0; s < KT / 4; ++s) {
+            double2 a[BX];
+            double as[BX];
+#pragma unroll
+            for (int x = 0; x < BX; ++x) {
+                a[x] = s_a[buf][wi * (16 * BX) + x * 16 + row][s * 4 + kq];
                 as[x] = a[x].x + a[x].y;
             }
+            const double2 b = s_b[buf][s * 4 + kq][wj * 16 + row];
+            const double bs = b.x + b.y;
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                b[y] = s_b[s * 4 + kq][wj * 32 + y * 16 + row];
-                bs[y] = b[y].x + b[y].y;
+            for (int x = 0; x < BX; ++x) {
+                p1[x] = mfma_f64(a[x].x, b.x, p1[x]);
+                p2[x] = mfma_f64(a[x].y, b.y, p2[x]);
+                p3[x] = mfma_f64(as[x], bs, p3[x]);
             }
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) {
-                    p1[x][y] = mfma_f64(a[x].x, b[y].x, p1[x][y]);
-                    p2[x][y] = mfma_f64(a[x].y, b[y].y, p2[x][y]);
-                    p3[x][y] = mfma_f64(as[x], bs[y], p3[x][y]);
-                }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
+    };
+    const int nst = nfull + (rem > 0);
+    auto fetch_any = [&](int st, int slot) {
+        if (st < nfull) fetch(slot);
+        else if (st < nst) fetch_rem(slot);
+    };
+    if (nst > 0) {
+        fetch_any(0, 0);
+        store(0, 0);
+        __syncthreads();
+#pragma unroll
+        for (int d = 1; d < PD; ++d) fetch_any(d, d % PD);
+        // stage st is multiplied from buffer st & 1, stage st + PD loaded
+        // (always a whole one here) and stage st + 1 written to LDS
+        int st = 0;
+        for (; st + PD + PD - 1 < nfull; st += PD) {
+#pragma unroll
+            for (int d = 0; d < PD; ++d) {
+                const int buf = d & 1;
+                __builtin_amdgcn_s_setprio(1);
+                fetch(d);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_setprio(2);
+                multiply(buf);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_setprio(0);
+                store((d + 1) % PD, buf ^ 1);
+                __syncthreads();
+            }
+        }
+        for (; st < nst; st += PD) {
+#pragma unroll
+            for (int d = 0; d < PD; ++d) {
+                if (st + d >= nst) break;
+                const int buf = d & 1;
+                fetch_any(st + d + PD, d);
+                multiply(buf);
+                if (st + d + 1 < nst) store((d + 1) % PD, buf ^ 1);
+                __syncthreads();
+            }
+        }
     }
+    double2* C = g.c + bz * g.stride_c;
     const bool use_beta = g.beta.x != 0.0 || g.beta.y != 0.0;
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < BX; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int r = i0 + wi * 32 + x * 16 + 4 * t + kq;
-                const int c = j0 + wj * 32 + y * 16 + row;
-                if (r >= g.m || c >= g.n) continue;
-                const double2 acc = make_double2(p1[x][y][t] - p2[x][y][t],
-                                                 p3[x][y][t] - p1[x][y][t] - p2[x][y][t]);
-                double2 v = cmul(g.alpha, acc);
-                double2* dst = C + static_cast<int64_t>(r) * g.ldc + c;
-                if (use_beta) {
-                    const double2 o = cmul(g.beta, *dst);
-                    v.x += o.x;
-                    v.y += o.y;
-                }
-                *dst = v;
+        for (int t = 0; t < 4; ++t) {
+            const int r = i0 + wi * (16 * BX) + x * 16 + 4 * t + kq;
+            const int c = j0 + wj * 16 + row;
+            if (r >= g.m || c >= g.n) continue;
+            const double2 acc =
+                make_double2(p1[x][t] - p2[x][t], p3[x][t] - p1[x][t] - p2[x][t]);
+            double2 v = cmul(g.alpha, acc);
+            double2* dst = C + static_cast<int64_t>(r) * g.ldc + c;
+            if (use_beta) {
+                const double2 o = cmul(g.beta, *dst);
+                v.x += o.x;
+                v.y += o.y;
             }
+            *dst = v;
+        }
 }
 
+template <int OPA, int OPB, int BX>
+void zgemm_tile_launch(const ZGemm& g, hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>(ceil_div(g.n, 32)),
+                    static_cast<unsigned>(ceil_div(g.m, 32 * BX)), static_cast<unsigned>(g.batch));
+    ProfScope ps("zgemm", s);
+    hipLaunchKernelGGL((zgemm_kernel<OPA, OPB, BX>), grid, dim3(256), 0, s, g);
+    GW_HIP_TRY(hipGetLastError());
+}
+
+// 64 x 32 tiles read fewer bytes per flop; 32 x 32 tiles make twice the
+// workgroups.  Below four 64 x 32 tiles per CU the second counts for more: 780
+// tiles (3840 x 400 x 2007) take 394 us wide and 359 us narrow, 1140
+// (3840 x 603 x 6031) 1516 and 1631 us.
 template <int OPA, int OPB>
 void zgemm_launch(const ZGemm& g, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>(ceil_div(g.n, 64)),
-                    static_cast<unsigned>(ceil_div(g.m, 64)), static_cast<unsigned>(g.batch));
-    ProfScope ps("zgemm", s);
-    hipLaunchKernelGGL((zgemm_kernel<OPA, OPB>), grid, dim3(256), 0, s, g);
-    GW_HIP_TRY(hipGetLastError());
+    const int64_t wide = static_cast<int64_t>(ceil_div(g.n, 32)) * ceil_div(g.m, 64) * g.batch;
+    if (wide >= 1024)
+        zgemm_tile_launch<OPA, OPB, 2>(g, s);
+    else
+        zgemm_tile_launch<OPA, OPB, 1>(g, s);
 }
 
 // z may alias x or y (elementwise), so the pointers are not restrict

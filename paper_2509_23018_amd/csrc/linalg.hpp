@@ -15,8 +15,8 @@ enum ZOp { kOpN = 0, kOpT = 1, kOpC = 2 };
 // C = alpha op(A) op(B) + beta C for `batch` independent products (pointers
 // advanced by the strides), row-major: op(A) is m x k, op(B) k x n, C m x n;
 // A is stored m x k (kOpN) or k x m (kOpT, kOpC) with leading dimension lda,
-// likewise B.  beta = 0 never reads C.  FP64 MFMA, 64 x 64 tiles, each complex
-// multiply-add as three real products.
+// likewise B.  beta = 0 never reads C.  FP64 MFMA, 64 x 32 or 32 x 32 tiles by
+// the size of C, each complex multiply-add as three real products.
 struct ZGemm {
     int m = 0, n = 0, k = 0;
     const double2* a = nullptr;

@@ -21,6 +21,28 @@ def _to(x):
     return torch.from_numpy(np.ascontiguousarray(x)).to(device())
 
 
+# k around the 16-deep stages (none, one, an odd and an even count, each with
+# and without a partial last one); m, n off and on the tile edges.  The batch
+# puts the same products on 64 x 32 tiles (from 1,024 of them on) and alone on
+# 32 x 32 tiles.
+@pytest.mark.parametrize("m,n,k", [(64, 32, 16), (65, 33, 1), (63, 31, 15), (33, 65, 17),
+                                   (1, 70, 32), (70, 1, 33), (40, 40, 48), (96, 64, 63),
+                                   (64, 64, 64), (31, 97, 95), (129, 33, 97)])
+def test_zgemm_tile_shapes_agree(m, n, k):
+    rng = np.random.default_rng(m + 100 * n + k)
+    batch = -(-1024 // (-(-m // 64) * -(-n // 32)))
+    a, b = _crand(rng, batch, m, k), _crand(rng, batch, k, n)
+    many = gw.gw_zgemm("N", "N", _to(a), _to(b)).cpu().numpy()
+    one = gw.gw_zgemm("N", "N", _to(a[-1]), _to(b[-1])).cpu().numpy()
+    assert np.array_equal(many[-1], one)      # a tile does not change the order of a sum
+    # k products and as many sums of rounded three-product terms per entry
+    assert rel_fro(many, a @ b) < 8 * EPS * np.sqrt(k + 1)
+    for op in ("T", "C"):
+        ta = _to(np.swapaxes(a if op == "T" else a.conj(), 1, 2))
+        tb = _to(np.swapaxes(b if op == "T" else b.conj(), 1, 2))
+        assert np.array_equal(gw.gw_zgemm(op, op, ta, tb).cpu().numpy(), many)
+
+
 # pivot blocks of 64: one row of them, a full one, one past, the last of 1 and
 # of 63, and (past 512) a second level
 @pytest.mark.parametrize("n", [1, 16, 17, 63, 64, 65, 127, 513, 575])
