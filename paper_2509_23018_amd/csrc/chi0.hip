@@ -49,9 +49,9 @@ constexpr int kKt = 16;     // pairs per LDS stage
 // rows of M for the tile's G and G' are staged in LDS (double-buffered; rows
 // padded by PAD elements), the G' side already multiplied by s*Delta_w(k);
 // the MFMAs accumulate conj(M_i) (Delta M_j), with three real products per
-// complex one on the 64x64 tile.  Loads are unconditional: pair
-// rows past the chunk end are clamped and carry Delta = 0, columns past N_G
-// are clamped and only feed outputs that are not stored.
+// complex one on the 64x64 tile.  Pair rows past the chunk end (in the last
+// stage) are clamped and carry Delta = 0, columns past N_G are clamped and only
+// feed outputs that are not stored.
 // mode: 0 overwrite, 1 accumulate.  PART: store the whole T x T tile instead,
 // unmasked, row-major at cw (a partial sum over a range of pairs).
 template <int T, int WI, int WJ, int PAD, bool PART = false>
@@ -74,7 +74,7 @@ __device__ __forceinline__ void f64_tile(double2* lds, const double2* __restrict
     // NT is a multiple of T, so cc is the same for every u and kk steps by NT/T
     constexpr int KSTEP = NT / T;
     const int cc = tid % T, kk0 = tid / T;
-    const int64_t ci = min(i0 + cc, ng - 1), cj = min(j0 + cc, ng - 1);
+    const int ci = min(i0 + cc, ng - 1), cj = min(j0 + cc, ng - 1);
 
     // conj(a) b with three real products where the registers allow
     // (Karatsuba, K3): p1 = ar br, p2 = ai bi, p3 = (ar - ai)(br + bi);
@@ -87,69 +87,91 @@ __device__ __forceinline__ void f64_tile(double2* lds, const double2* __restrict
 #pragma unroll
         for (int b = 0; b < BY; ++b) p1[a][b] = p2[a][b] = p3[a][b] = zero4();
 
-    double2 ra[NLOAD], rb[NLOAD];
-
-    // stage 0
-#pragma unroll
-    for (int u = 0; u < NLOAD; ++u) {
-        const int64_t k = kk0 + KSTEP * u;
-        const int64_t kr = k < kc ? k : kc - 1;
-        const double2 d = k < kc ? dw[kr] : make_double2(0.0, 0.0);
-        s_a[(kk0 + KSTEP * u) * LDR + cc] = m[kr * ng + ci];
-        s_b[(kk0 + KSTEP * u) * LDR + cc] = cmul(d, m[kr * ng + cj]);
-    }
-    __syncthreads();
-    int buf = 0;
-    const int nsteps = static_cast<int>((kc + kKt - 1) / kKt);
-    for (int st = 0; st < nsteps; ++st) {
-        // unconditional (clamped) prefetch of the next stage keeps the loop
-        // free of branches, so the compiler cannot merge the LDS stores into
-        // the load block
-        // issue priority: 1 while the next stage's loads are issued, 2 over
-        // the MFMA block, 0 for the LDS stores and the barrier; of the two
-        // waves on a SIMD the one with MFMAs to issue goes first, the other
-        // fills the gaps (6.20 -> 5.59 ms per 48^3 chunk)
-        __builtin_amdgcn_s_setprio(1);
-        const int64_t k1 = static_cast<int64_t>(st + 1) * kKt;
-        double2 rd[NLOAD];
-#pragma unroll
-        for (int u = 0; u < NLOAD; ++u) {
-            const int64_t k = k1 + kk0 + KSTEP * u;
-            const int64_t kr = k < kc ? k : kc - 1;
-            rd[u] = dw[kr];
-            rb[u] = m[kr * ng + cj];
+    // Loads of a whole stage go through addresses that are uniform but for a
+    // 32-bit offset per lane, fixed for the tile.
+    const uint32_t voi = static_cast<uint32_t>((kk0 * ng + ci) * sizeof(double2));
+    const uint32_t voj = static_cast<uint32_t>((kk0 * ng + cj) * sizeof(double2));
+    const uint32_t vod = static_cast<uint32_t>(kk0 * sizeof(double2));
+    const int64_t row_bytes = static_cast<int64_t>(ng) * sizeof(double2);
+    double2 ra[NLOAD], rb[NLOAD], rd[NLOAD];
+    // load l (of 3 NLOAD) of whole stage st: Delta, the G' and the G side of
+    // staged row l / 3
+    auto load = [&](int st, int l) {
+        const int u = l / 3;
+        const int64_t k = static_cast<int64_t>(st) * kKt + KSTEP * u;
+        const char* pm = reinterpret_cast<const char*>(m) + k * row_bytes;
+        if (l % 3 == 0) {
+            rd[u] = *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(dw + k) + vod);
+        } else if (l % 3 == 1) {
+            rb[u] = *reinterpret_cast<const double2*>(pm + voj);
+        } else {
             // component loads: a whole-struct copy into LDS would be fused
             // into one global-to-LDS copy placed after the MFMAs, exposing
             // the load latency at every stage
-            ra[u].x = m[kr * ng + ci].x;
-            ra[u].y = m[kr * ng + ci].y;
+            const double2* pa = reinterpret_cast<const double2*>(pm + voi);
+            ra[u].x = pa->x;
+            ra[u].y = pa->y;
         }
-        // loads first, then the MFMAs of the current stage (no reordering)
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(2);
+    };
+    const int nfull = static_cast<int>(kc / kKt);
+    const int nst = static_cast<int>((kc + kKt - 1) / kKt);
+    auto fetch = [&](int st) {
+        if (st < nfull) {
 #pragma unroll
-        for (int s = 0; s < kKt / 4; ++s) {
-            const double2* la = s_a + (buf * kKt + s * 4 + kq) * LDR + wi * (T / WI) + row;
-            const double2* lb = s_b + (buf * kKt + s * 4 + kq) * LDR + wj * (T / WJ) + row;
+            for (int l = 0; l < 3 * NLOAD; ++l) load(st, l);
+        } else if (st < nst) {  // the last, partial stage: rows past the end are clamped
+#pragma unroll
+            for (int u = 0; u < NLOAD; ++u) {
+                const int64_t k = static_cast<int64_t>(st) * kKt + kk0 + KSTEP * u;
+                const int64_t kr = k < kc ? k : kc - 1;
+                rd[u] = k < kc ? dw[kr] : make_double2(0.0, 0.0);
+                rb[u] = k < kc ? m[kr * ng + cj] : make_double2(0.0, 0.0);
+                ra[u] = m[kr * ng + ci];
+            }
+        }
+    };
+    auto store = [&](int u, int buf) {
+        s_a[(buf * kKt + kk0 + KSTEP * u) * LDR + cc] = make_double2(ra[u].x, ra[u].y);
+        s_b[(buf * kKt + kk0 + KSTEP * u) * LDR + cc] = cmul(rd[u], rb[u]);
+    };
+    auto store_all = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < NLOAD; ++u) store(u, buf);
+    };
+    // fragments of k-step q, and the sums of the third product
+    auto read = [&](int buf, int q, double2 (&a)[BX], double2 (&b)[BY]) {
+        const double2* la = s_a + (buf * kKt + q * 4 + kq) * LDR + wi * (T / WI) + row;
+        const double2* lb = s_b + (buf * kKt + q * 4 + kq) * LDR + wj * (T / WJ) + row;
+#pragma unroll
+        for (int x = 0; x < BX; ++x) a[x] = la[x * 16];
+#pragma unroll
+        for (int y = 0; y < BY; ++y) b[y] = lb[y * 16];
+    };
+    auto sums = [&](const double2 (&a)[BX], const double2 (&b)[BY], double (&as)[BX],
+                    double (&bs)[BY]) {
+#pragma unroll
+        for (int x = 0; x < BX; ++x) as[x] = a[x].x - a[x].y;
+#pragma unroll
+        for (int y = 0; y < BY; ++y) bs[y] = b[y].x + b[y].y;
+    };
+    // MFMA i of the 3 BX BY of a k-step (K3)
+    auto mfma_k3 = [&](int i, const double2 (&a)[BX], const double2 (&b)[BY],
+                       const double (&as)[BX], const double (&bs)[BY]) {
+        const int x = i / 3 / BY, y = i / 3 % BY;
+        if (i % 3 == 0) p1[x][y] = mfma_f64(a[x].x, b[y].x, p1[x][y]);
+        if (i % 3 == 1) p2[x][y] = mfma_f64(a[x].y, b[y].y, p2[x][y]);
+        if (i % 3 == 2) p3[x][y] = mfma_f64(as[x], bs[y], p3[x][y]);
+    };
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < kKt / 4; ++q) {
             double2 a[BX], b[BY];
-#pragma unroll
-            for (int x = 0; x < BX; ++x) a[x] = la[x * 16];
-#pragma unroll
-            for (int y = 0; y < BY; ++y) b[y] = lb[y * 16];
+            read(buf, q, a, b);
             if constexpr (K3) {
                 double as[BX], bs[BY];
+                sums(a, b, as, bs);
 #pragma unroll
-                for (int x = 0; x < BX; ++x) as[x] = a[x].x - a[x].y;
-#pragma unroll
-                for (int y = 0; y < BY; ++y) bs[y] = b[y].x + b[y].y;
-#pragma unroll
-                for (int x = 0; x < BX; ++x)
-#pragma unroll
-                    for (int y = 0; y < BY; ++y) {
-                        p1[x][y] = mfma_f64(a[x].x, b[y].x, p1[x][y]);
-                        p2[x][y] = mfma_f64(a[x].y, b[y].y, p2[x][y]);
-                        p3[x][y] = mfma_f64(as[x], bs[y], p3[x][y]);
-                    }
+                for (int i = 0; i < 3 * BX * BY; ++i) mfma_k3(i, a, b, as, bs);
             } else {
 #pragma unroll
                 for (int x = 0; x < BX; ++x)
@@ -158,20 +180,72 @@ __device__ __forceinline__ void f64_tile(double2* lds, const double2* __restrict
                         cmfma_conj_a(p1[x][y], p2[x][y], a[x].x, a[x].y, b[y].x, b[y].y);
             }
         }
-        // keep the LDS stores of the next stage after this stage's MFMAs, so
-        // the global loads issued above stay in flight during the compute
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
-        const int nb2 = buf ^ 1;
+    };
+
+    // Stage st + 1 is loaded while stage st is multiplied and written to the
+    // other LDS buffer behind the loads.  The wave issues in order and shares
+    // its SIMD with one other, so what stands between two MFMAs decides how
+    // long the matrix pipe waits.
+    fetch(0);
+    store_all(0);
+    __syncthreads();
+    int st = 0;
+    if constexpr (K3) {
+        // Every instruction between the MFMAs of a whole stage is placed: six
+        // loads in each of the first k-steps, one per two MFMAs; the next
+        // k-step's fragments read after the ninth MFMA and their sums formed
+        // before the last; in the last k-step one staged row written to LDS
+        // per two MFMAs.  The same work with the loads and the LDS writes each
+        // in one run before and after the MFMAs takes 64.0 ms where this takes
+        // 58.7 (3,840 pairs of the 72^3 grid, 6,031 G, 8 frequencies, MTXEL
+        // among them; 60.2 with the address arithmetic between the loads).
+        constexpr int NM = 3 * BX * BY, NQ = kKt / 4, LD = NM / 2;
+        static_assert(NQ * LD >= 3 * NLOAD && NM / 2 > NLOAD, "no room for a stage's loads");
+        double2 a[2][BX], b[2][BY];
+        double as[2][BX], bs[2][BY];
+        for (; st + 1 < nfull; ++st) {
+            const int buf = st & 1;
+            read(buf, 0, a[0], b[0]);
+            sums(a[0], b[0], as[0], bs[0]);
+            __builtin_amdgcn_s_setprio(2);  // over the other workgroup's barrier and first reads
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < NLOAD; ++u) {
-            const int64_t k = k1 + kk0 + KSTEP * u;
-            s_a[(nb2 * kKt + kk0 + KSTEP * u) * LDR + cc] = make_double2(ra[u].x, ra[u].y);
-            s_b[(nb2 * kKt + kk0 + KSTEP * u) * LDR + cc] =
-                k < kc ? cmul(rd[u], rb[u]) : make_double2(0.0, 0.0);
+            for (int q = 0; q < NQ; ++q) {
+                const int f = q & 1;
+#pragma unroll
+                for (int i = 0; i < NM; ++i) {
+                    mfma_k3(i, a[f], b[f], as[f], bs[f]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int l = q * LD + i / 2;
+                    if (i % 2 == 1 && l < 3 * NLOAD) load(st + 1, l);
+                    if (i == NM - 4 && q + 1 < NQ) read(buf, q + 1, a[f ^ 1], b[f ^ 1]);
+                    if (i == NM - 2 && q + 1 < NQ) sums(a[f ^ 1], b[f ^ 1], as[f ^ 1], bs[f ^ 1]);
+                    if (q + 1 == NQ && i % 2 == 0 && i >= 2 && i / 2 <= NLOAD)
+                        store(i / 2 - 1, buf ^ 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_s_setprio(0);
+            __syncthreads();
         }
+    } else {
+        for (; st + 1 < nfull; ++st) {
+            __builtin_amdgcn_s_setprio(1);
+            fetch(st + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(2);
+            multiply(st & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+            store_all((st & 1) ^ 1);
+            __syncthreads();
+        }
+    }
+    for (; st < nst; ++st) {  // the last whole stage and the partial one
+        fetch(st + 1);
+        multiply(st & 1);
+        if (st + 1 < nst) store_all((st & 1) ^ 1);
         __syncthreads();
-        buf = nb2;
     }
 #pragma unroll
     for (int x = 0; x < BX; ++x)
@@ -273,7 +347,7 @@ __global__ __launch_bounds__(WI * WJ * 64) void chi0_f64_batched_kernel(
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
         __syncthreads();
-        const int it = s_item;
+        const int it = __builtin_amdgcn_readfirstlane(s_item);
         __syncthreads();
         if (it >= nitems) break;
         const int4 itm = items[it];
