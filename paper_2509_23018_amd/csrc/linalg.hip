@@ -28,12 +28,12 @@ namespace {
 // stages where it does not.  Measured against 64 x 64 tiles of one LDS buffer,
 // loads one stage ahead and clamps and masks in every stage (TFLOP/s count the
 // six flops executed per complex multiply-add):
-//   2048 x 2048 x 2048        960 ->  774 us (53.7 -> 66.6 TFLOP/s), BX = 2
-//   4 of 2007 x 2007 x 512    914 ->  805 us (54.2 -> 61.5)
-//   3840 x 603 x 6031        2630 -> 1516 us (31.9 -> 55.3)
-//   3840 x 400 x 2007         445 ->  359 us (41.6 -> 51.5), BX = 1
-//   1189 x 135 x 1189         154 ->   44 us,                BX = 1
-//   135 x 135 x 1189          158 ->   46 us,                BX = 1
+//   2048 x 2048 x 2048        960 ->  800 us (53.7 -> 64.4 TFLOP/s), BX = 2
+//   4 of 2007 x 2007 x 512    914 ->  815 us (54.2 -> 60.7)
+//   3840 x 603 x 6031        2630 -> 1424 us (31.9 -> 58.9)
+//   3840 x 400 x 2007         445 ->  352 us (41.6 -> 52.5), BX = 1
+//   1189 x 135 x 1189         154 ->   38 us,                BX = 1
+//   135 x 135 x 1189          158 ->   37 us,                BX = 1
 // Writing stage t + 1 to LDS before the MFMAs of stage t (915 us for the
 // first) and 32-deep stages (47 us for the fifth) were slower.
 
@@ -84,19 +84,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void z
     double2 ra[PD][NA], rb[PD][NB];
     // component loads: a whole-struct copy would be fused with the LDS write
     // into one copy behind the MFMAs
+    auto load = [&](int slot, int e) {  // element e of NA + NB
+        if (e < NA) {
+            ra[slot][e].x = pa[e]->x;
+            ra[slot][e].y = pa[e]->y;
+            pa[e] += da;
+        } else {
+            rb[slot][e - NA].x = pb[e - NA]->x;
+            rb[slot][e - NA].y = pb[e - NA]->y;
+            pb[e - NA] += db;
+        }
+    };
     auto fetch = [&](int slot) {
 #pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            ra[slot][u].x = pa[u]->x;
-            ra[slot][u].y = pa[u]->y;
-            pa[u] += da;
-        }
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            rb[slot][u].x = pb[u]->x;
-            rb[slot][u].y = pb[u]->y;
-            pb[u] += db;
-        }
+        for (int e = 0; e < NA + NB; ++e) load(slot, e);
     };
     const int nfull = g.k / KT, rem = g.k % KT;
     auto fetch_rem = [&](int slot) {  // the last, partial stage: k past the end is zero
@@ -113,40 +114,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void z
             rb[slot][u] = kk < rem ? *pb[u] : make_double2(0.0, 0.0);
         }
     };
+    auto store1 = [&](int slot, int buf, int e) {
+        if (e < NA) {
+            int mm, kk;
+            a_mk(e, mm, kk);
+            const double2 v = ra[slot][e];
+            s_a[buf][mm][kk] = make_double2(v.x, OPA == kOpC ? -v.y : v.y);
+        } else {
+            int kk, nn;
+            b_kn(e - NA, kk, nn);
+            const double2 v = rb[slot][e - NA];
+            s_b[buf][kk][nn] = make_double2(v.x, OPB == kOpC ? -v.y : v.y);
+        }
+    };
     auto store = [&](int slot, int buf) {
 #pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            int mm, kk;
-            a_mk(u, mm, kk);
-            s_a[buf][mm][kk] = make_double2(ra[slot][u].x, OPA == kOpC ? -ra[slot][u].y
-                                                                       : ra[slot][u].y);
-        }
+        for (int e = 0; e < NA + NB; ++e) store1(slot, buf, e);
+    };
+    // fragments of k-step q, and the sums of the third product
+    auto read = [&](int buf, int q, double2 (&a)[BX], double2& b) {
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            int kk, nn;
-            b_kn(u, kk, nn);
-            s_b[buf][kk][nn] = make_double2(rb[slot][u].x, OPB == kOpC ? -rb[slot][u].y
-                                                                       : rb[slot][u].y);
-        }
+        for (int x = 0; x < BX; ++x) a[x] = s_a[buf][wi * (16 * BX) + x * 16 + row][q * 4 + kq];
+        b = s_b[buf][q * 4 + kq][wj * 16 + row];
+    };
+    auto sums = [&](const double2 (&a)[BX], double2 b, double (&as)[BX], double& bs) {
+#pragma unroll
+        for (int x = 0; x < BX; ++x) as[x] = a[x].x + a[x].y;
+        bs = b.x + b.y;
+    };
+    auto mfma1 = [&](int i, const double2 (&a)[BX], double2 b, const double (&as)[BX], double bs) {
+        const int x = i / 3;
+        if (i % 3 == 0) p1[x] = mfma_f64(a[x].x, b.x, p1[x]);
+        if (i % 3 == 1) p2[x] = mfma_f64(a[x].y, b.y, p2[x]);
+        if (i % 3 == 2) p3[x] = mfma_f64(as[x], bs, p3[x]);
     };
     auto multiply = [&](int buf) {
 #pragma unroll
-        for (int s = 0; s < KT / 4; ++s) {
-            double2 a[BX];
-            double as[BX];
+        for (int q = 0; q < KT / 4; ++q) {
+            double2 a[BX], b;
+            double as[BX], bs;
+            read(buf, q, a, b);
+            sums(a, b, as, bs);
 #pragma unroll
-            for (int x = 0; x < BX; ++x) {
-                a[x] = s_a[buf][wi * (16 * BX) + x * 16 + row][s * 4 + kq];
-                as[x] = a[x].x + a[x].y;
-            }
-            const double2 b = s_b[buf][s * 4 + kq][wj * 16 + row];
-            const double bs = b.x + b.y;
-#pragma unroll
-            for (int x = 0; x < BX; ++x) {
-                p1[x] = mfma_f64(a[x].x, b.x, p1[x]);
-                p2[x] = mfma_f64(a[x].y, b.y, p2[x]);
-                p3[x] = mfma_f64(as[x], bs, p3[x]);
-            }
+            for (int i = 0; i < 3 * BX; ++i) mfma1(i, a, b, as, bs);
         }
     };
     const int nst = nfull + (rem > 0);
@@ -160,21 +170,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void z
         __syncthreads();
 #pragma unroll
         for (int d = 1; d < PD; ++d) fetch_any(d, d % PD);
-        // stage st is multiplied from buffer st & 1, stage st + PD loaded
-        // (always a whole one here) and stage st + 1 written to LDS
+        // Stage st is multiplied from buffer st & 1, stage st + PD loaded
+        // (always a whole one here) and stage st + 1 written to LDS.  Every
+        // instruction between the MFMAs is placed: one load per two MFMAs from
+        // the start of the stage, one LDS write per MFMA at its end, the next
+        // k-step's fragments and sums before the current one ends.  In runs
+        // before and after the MFMAs the same instructions made the fifth
+        // product above take 44 us where it now takes 38, the first 842 and
+        // 800 us on one box.
         int st = 0;
         for (; st + PD + PD - 1 < nfull; st += PD) {
 #pragma unroll
             for (int d = 0; d < PD; ++d) {
                 const int buf = d & 1;
-                __builtin_amdgcn_s_setprio(1);
-                fetch(d);
-                __builtin_amdgcn_sched_barrier(0);
+                constexpr int NM = 3 * BX, NQ = KT / 4, NE = NA + NB;
+                double2 a[2][BX], b[2];
+                double as[2][BX], bs[2];
+                read(buf, 0, a[0], b[0]);
+                sums(a[0], b[0], as[0], bs[0]);
                 __builtin_amdgcn_s_setprio(2);
-                multiply(buf);
                 __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int f = q & 1;
+#pragma unroll
+                    for (int i = 0; i < NM; ++i) {
+                        mfma1(i, a[f], b[f], as[f], bs[f]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const int t = q * NM + i;
+                        const int w = t - (NQ * NM - NE - 1);
+                        if (t % 2 == 1 && t / 2 < NE) load(d, t / 2);
+                        if (w >= 0 && w < NE) store1((d + 1) % PD, buf ^ 1, w);
+                        if (i == (NM - 2) / 2 && q + 1 < NQ) read(buf, q + 1, a[f ^ 1], b[f ^ 1]);
+                        if (i == NM - 2 && q + 1 < NQ) sums(a[f ^ 1], b[f ^ 1], as[f ^ 1], bs[f ^ 1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
                 __builtin_amdgcn_s_setprio(0);
-                store((d + 1) % PD, buf ^ 1);
                 __syncthreads();
             }
         }
