@@ -8,17 +8,24 @@
 
 namespace gw {
 
-// Energies per launch (the first GEMM's output for a batch stays within 1 GiB).
-int gpp_energy_batch(int ns, int ng, int ne);
-// Device scratch of run_gpp_sigma.
-size_t gpp_bytes(int ns, int ng, int ne);
+// One launch holds ec energies of bc bands; scratch: T of every (band, energy)
+// pair at 0, with bc > 1 their products T M^T at off_part, the energies (device
+// copy, [ne]) at off_e, total bytes in all.
+struct GppLayout {
+    int ec = 1, bc = 1;
+    size_t off_part = 0, off_e = 0, total = 0;
+};
+// The layout for nb bands in a workspace of `bytes` (0: the library's scratch).
+// Any workspace that holds one band (nb = 1) will do; a larger one takes more
+// bands per launch.
+GppLayout gpp_layout(int ns, int ng, int nb, int ne, size_t bytes);
 
 // sigma[e] (device [ne][ns][ns], overwritten) = sum_n conj(M_n) P^{n e} M_n^T
-// with M device [nb][ns][ng], e_n and occupied host [nb], energies_dev device
-// [ne] (complex), omega2 device [ng][ng], wt device [ng][ng], v device [ng].
+// with M device [nb][ns][ng], e_n and occupied host [nb], omega2 device
+// [ng][ng], wt device [ng][ng], v device [ng]; the energies are at base +
+// L.off_e.
 void run_gpp_sigma(const double2* m, int nb, int ns, int ng, const double* e_n,
-                   const int32_t* occupied, const double2* energies_dev, int ne,
-                   const double2* omega2, const double* wt, const double* v, double2* sigma,
-                   char* base, hipStream_t s);
+                   const int32_t* occupied, int ne, const double2* omega2, const double* wt,
+                   const double* v, double2* sigma, char* base, const GppLayout& L, hipStream_t s);
 
 }  // namespace gw

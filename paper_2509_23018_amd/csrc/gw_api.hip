@@ -1864,7 +1864,7 @@ gw_status_t gw_epsinv(const gw_c128* chi, int32_t ng, int32_t nz, const double* 
 
 size_t gw_gpp_sigma_workspace_bytes(int32_t ns, int32_t ng, int32_t ne) {
     if (ns < 0 || ng < 0 || ne < 1) return static_cast<size_t>(-1);
-    return gpp_bytes(ns, ng, ne);
+    return gpp_layout(ns, ng, 1, ne, 0).total;
 }
 
 gw_status_t gw_gpp_sigma(const gw_c128* m, int32_t nb, int32_t ns, int32_t ng,
@@ -1890,15 +1890,15 @@ gw_status_t gw_gpp_sigma(const gw_c128* m, int32_t nb, int32_t ns, int32_t ng,
         if (o.ws && (reinterpret_cast<uintptr_t>(o.ws) & 255))
             fail(GW_EINVAL, "workspace must be 256-byte aligned");
         hipStream_t s = static_cast<hipStream_t>(stream);
-        const size_t need = gpp_bytes(ns, ng, ne);
-        char* base = call_scratch(need, o, s);
-        // the energies follow the first-GEMM buffer, staged in stream order
-        const size_t e_off = need - ((static_cast<size_t>(ne) * sizeof(double2) + 255) & ~size_t(255));
-        stage_h2d(base + e_off, energies, static_cast<size_t>(ne) * sizeof(double2), s);
-        run_gpp_sigma(reinterpret_cast<const double2*>(m), nb, ns, ng, e_n, occupied,
-                      reinterpret_cast<const double2*>(base + e_off), ne,
+        // a workspace has to hold one band per launch, and takes more if it can
+        GppLayout L = gpp_layout(ns, ng, 1, ne, 0);
+        if (!o.ws || o.ws_bytes >= L.total) L = gpp_layout(ns, ng, nb, ne, o.ws_bytes);
+        char* base = call_scratch(L.total, o, s);
+        // the energies follow the GEMMs' buffers, staged in stream order
+        stage_h2d(base + L.off_e, energies, static_cast<size_t>(ne) * sizeof(double2), s);
+        run_gpp_sigma(reinterpret_cast<const double2*>(m), nb, ns, ng, e_n, occupied, ne,
                       reinterpret_cast<const double2*>(omega2), wtilde, vcoul,
-                      reinterpret_cast<double2*>(sigma), base, s);
+                      reinterpret_cast<double2*>(sigma), base, L, s);
     });
 }
 

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void z
         int kk, nn;
         b_kn(u, kk, nn);
         const int64_t in = min(j0 + nn, g.n - 1);
-        pb[u] = g.b + bz * g.stride_b + (OPB == kOpN ? kk * g.ldb + in : in * g.ldb + kk);
+        pb[u] = g.b + bz / g.b_repeat * g.stride_b + (OPB == kOpN ? kk * g.ldb + in : in * g.ldb + kk);
     }
     const int64_t da = OPA == kOpN ? KT : KT * g.lda, db = OPB == kOpN ? KT * g.ldb : KT;
     double2 ra[PD][NA], rb[PD][NB];

@@ -28,6 +28,7 @@ struct ZGemm {
     double2 alpha = {1.0, 0.0};
     double2 beta = {0.0, 0.0};
     int batch = 1;
+    int b_repeat = 1;  // products that share one B: product i takes B number i / b_repeat
 };
 void launch_zgemm(ZOp opa, ZOp opb, const ZGemm& g, hipStream_t s);
 

@@ -1,12 +1,15 @@
 """The dense FP64 building blocks at the edges of their tiles and blocks: the
 two tile shapes of the complex GEMM, the register-resident pivot-block inverse
-of eps^-1 and the Cholesky blocks of Diag, against NumPy."""
+of eps^-1, the Cholesky blocks of Diag and the GPP kernel's row tiles and band
+batches, against NumPy and the oracle."""
 import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2509_23018_amd as gw
-from gpu_helpers import device, rel_fro
+from gpu_helpers import FP64_TOL, device, rel_fro
+from workloads import gen
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +82,27 @@ def test_diag_cholesky_blocks(n_eig, guard, rank):
     assert np.abs(w + ev[:n_eig]).max() < res
     assert np.abs(basis.conj().T @ basis - np.eye(n_eig)).max() < 1e-13
     assert np.linalg.norm(chi @ basis - basis * w, axis=0).max() < 1.01 * res
+
+
+# ns on the four row-tile heights and past them; ng without a whole 16-row
+# stage, with one, two, an odd number of them, and remainders; more bands than a
+# launch holds (64).  An exact-size workspace holds one band per launch.
+@pytest.mark.parametrize("nb,ns,ng,ne", [(3, 1, 1, 2), (2, 16, 15, 3), (2, 17, 16, 1),
+                                         (3, 32, 33, 2), (2, 33, 48, 2), (2, 48, 65, 3),
+                                         (2, 49, 79, 2), (2, 64, 112, 1), (2, 65, 130, 2),
+                                         (67, 5, 40, 2)])
+def test_gpp_tiles_and_bands(nb, ns, ng, ne):
+    inp = gen.gpp_inputs(nb, ns, ng, ne, seed=nb + ns + ng)
+    want = oracle.gpp_sigma_offdiag(inp["m"], inp["e_n"], inp["occupied"], inp["energies"],
+                                    inp["omega2"], inp["wtilde"], inp["v"])
+    d = {k: _to(inp[k]) for k in ("m", "omega2", "wtilde", "v")}
+    args = (d["m"], inp["e_n"], inp["occupied"], inp["energies"], d["omega2"], d["wtilde"], d["v"])
+    assert rel_fro(gw.gw_gpp_sigma(*args).cpu().numpy(), want) < FP64_TOL
+    need = int(gw.lib().gw_gpp_sigma_workspace_bytes(ns, ng, ne))
+    ws = gw.new_workspace(need + 256, device())
+    ws[need:] = 7
+    got = gw.gw_gpp_sigma(*args, workspace=ws[:need])
+    assert rel_fro(got.cpu().numpy(), want) < FP64_TOL
+    assert bool((ws[need:] == 7).all())
+    with pytest.raises(gw.GWError):
+        gw.gw_gpp_sigma(*args, workspace=ws[:need - 256])
