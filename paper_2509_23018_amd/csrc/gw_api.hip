@@ -1982,7 +1982,7 @@ gw_status_t gw_heev(const gw_c128* a, int32_t n, int32_t batch, double* w, gw_c1
         int* perm_d = reinterpret_cast<int*>(base + abytes + jacobi_work_bytes(n, batch));
         GW_HIP_TRY(hipMemcpyAsync(ac, a, nn * batch * sizeof(double2), hipMemcpyDeviceToDevice, s));
         double2* vtmp = reinterpret_cast<double2*>(v);
-        (void)jacobi_eigh(ac, vtmp, n, batch, tol > 0.0 ? tol : 1e-15, 100, jw, s);
+        (void)jacobi_eigh(ac, vtmp, n, batch, tol > 0.0 ? tol : 1e-15, 100, jw, s, false);
         // eigenvalues in increasing order, eigenvectors to match
         // (the diagonals gathered into w on the device, then one plain copy)
         std::vector<double> dg(static_cast<size_t>(n) * batch);

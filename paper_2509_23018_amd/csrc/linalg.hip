@@ -438,12 +438,14 @@ __global__ __launch_bounds__(256) void zero_fill_kernel(double2* __restrict__ p,
 // tau = (h_qq - h_pp) / (2 |b|), t = sign(tau) / (|tau| + sqrt(1 + tau^2)),
 // c = 1 / sqrt(1 + t^2), S = t c e^{i phi}; J = [[c, S], [-conj(S), c]] on
 // (p, q) makes (J^H H J)_pq = 0.  One step applies the n'/2 disjoint
-// rotations at once: A <- J^H A J and V <- V J.  A and V are read from one
-// buffer and written to the other (the rotation of every pair is computed from
-// the read buffer by each thread that needs it), so a step is one launch.
+// rotations at once: A <- J^H A J and V <- V J.
 
-__device__ __forceinline__ int rr_index(int j, int r, int np) {
-    return j == 0 ? 0 : 1 + (j - 1 + r) % (np - 1);
+// From n = kBJMin on by blocks of kBJ indices, below that by elements.
+constexpr int kBJ = 16, kBP = 2 * kBJ, kBJMin = 64;
+
+__device__ __forceinline__ int rr_index(int j, int r, int np) {  // j < np, r < np - 1
+    const int x = j - 1 + r;
+    return j == 0 ? 0 : 1 + (x >= np - 1 ? x - (np - 1) : x);
 }
 
 __device__ __forceinline__ void rr_pair(int k, int r, int np, int& p, int& q) {
@@ -478,86 +480,184 @@ __device__ __forceinline__ Rot rotation_of(double hpp, double hqq, double2 b) {
     return r;
 }
 
-__device__ __forceinline__ Rot rotation(const double2* __restrict__ a, int n, int p, int q) {
-    if (q >= n) return Rot{1.0, make_double2(0.0, 0.0)};
-    return rotation_of(a[static_cast<int64_t>(p) * n + p].x, a[static_cast<int64_t>(q) * n + q].x,
-                       a[static_cast<int64_t>(p) * n + q]);
+// The same rotation with one square root, one division and one reciprocal
+// square root in the chain: with d = h_qq - h_pp, u = t / |b| =
+// 2 sign(d) / (|d| + sqrt(d^2 + 4 |b|^2)), so that t^2 = u^2 |b|^2 and
+// S = c u b need no |b|.  1 + t^2 lies in [1, 2]: c from the hardware's
+// reciprocal square root and two Newton steps, then the exact one above.
+__device__ __forceinline__ Rot rotation_short(double hpp, double hqq, double2 b) {
+    Rot r{1.0, make_double2(0.0, 0.0)};
+    const double b2 = b.x * b.x + b.y * b.y;
+    if (b2 == 0.0) return r;
+    const double d = hqq - hpp;
+    const double u = (d >= 0.0 ? 2.0 : -2.0) / (fabs(d) + sqrt(fma(d, d, 4.0 * b2)));
+    const double ub = u * b2, qq = u * ub, x = 1.0 + qq;  // qq = t^2
+    double c0 = __builtin_amdgcn_rsq(x);
+    c0 = fma(c0, 0.5 * fma(-x * c0, c0, 1.0), c0);
+    c0 = fma(c0, 0.5 * fma(-x * c0, c0, 1.0), c0);
+    const double qe = fma(u, ub, -qq);
+    const double pp = c0 * c0, pe = fma(c0, c0, -pp);
+    const double res = (pp - 1.0) + pe + fma(pp, qq, pp * qe + pe * qq);
+    const double c = c0 - 0.5 * c0 * res;
+    const double sc = u * c;
+    r.c = c;
+    r.s = make_double2(sc * b.x, sc * b.y);
+    return r;
 }
 
-// blocks [0, na): 2 x 2 blocks (k1, k2) of A; blocks [na, ...): (row, pair) of V
-__global__ __launch_bounds__(256) void jacobi_step_kernel(const double2* __restrict__ a_in,
-                                                          double2* __restrict__ a_out,
-                                                          const double2* __restrict__ v_in,
-                                                          double2* __restrict__ v_out, int n,
-                                                          int np, int r, int64_t na_threads,
-                                                          int64_t batch_stride) {
-    const int64_t bz = blockIdx.z;
-    a_in += bz * batch_stride;
-    a_out += bz * batch_stride;
-    v_in += bz * batch_stride;
-    v_out += bz * batch_stride;
-    const int half = np / 2;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t < na_threads) {
-        const int k1 = static_cast<int>(t / half), k2 = static_cast<int>(t % half);
+// Whole eigen-decomposition of one n x n matrix (n < kBJMin) by one workgroup,
+// A and V in LDS: element sweeps in round-robin order until the off-diagonal
+// norm is below tol of the norm or has stopped falling at roundoff (the
+// criterion of jacobi_eigh), at most max_sweeps.  SHORT picks the rotation; NT
+// threads are at least one per 2 x 2 block of A.
+//
+// A chain of n - 1 dependent steps per sweep, each the latency of a rotation
+// (one wave) and of the update of A (every wave); V is updated with the
+// previous step's rotations beside the next ones.  As a launch per step, with
+// A and V in global memory and a host wait per sweep, a step took 5.4 us (24
+// matrices of n = 48: 2,340 us) against 1.35 us here (670 us).  Updating only
+// the upper blocks of A and writing their mirror images took as long.
+template <bool SHORT, int NT>
+__global__ __launch_bounds__(NT) void jacobi_lds_kernel(double2* __restrict__ a_io,
+                                                         double2* __restrict__ v_io, int n,
+                                                         double tol, int max_sweeps,
+                                                         double* __restrict__ sweeps_out) {
+    extern __shared__ double2 jl[];
+    constexpr int NW = NT / 64;
+    __shared__ double s_red[2 * NW];
+    __shared__ double rc[2][kBJMin / 2];
+    __shared__ double2 rs[2][kBJMin / 2];
+    const int ld = n | 1;  // odd row length: columns fall on different banks
+    double2* a = jl;
+    double2* v = jl + n * ld;
+    const int np = n + (n & 1), half = np / 2;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    a_io += static_cast<int64_t>(blockIdx.x) * n * n;
+    v_io += static_cast<int64_t>(blockIdx.x) * n * n;
+    for (int e = tid; e < n * n; e += NT) {
+        const int i = e / n, j = e % n;
+        a[i * ld + j] = a_io[e];
+        v[i * ld + j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
+    }
+    __syncthreads();
+    auto rotations = [&](int r, int buf) {  // one wave
+        if (lane >= half) return;
+        int p, q;
+        rr_pair(lane, r, np, p, q);
+        Rot ro{1.0, make_double2(0.0, 0.0)};
+        if (q < n) {
+            const double hpp = a[p * ld + p].x, hqq = a[q * ld + q].x;
+            ro = SHORT ? rotation_short(hpp, hqq, a[p * ld + q])
+                       : rotation_of(hpp, hqq, a[p * ld + q]);
+        }
+        rc[buf][lane] = ro.c;
+        rs[buf][lane] = ro.s;
+    };
+    // right: [x_p, x_q] <- [c x_p - conj(S) x_q, S x_p + c x_q]
+    auto right = [](double c, double2 sx, double2 xp, double2 xq, double2& op, double2& oq) {
+        const double2 u = cmul(make_double2(sx.x, -sx.y), xq), w = cmul(sx, xp);
+        op = make_double2(c * xp.x - u.x, c * xp.y - u.y);
+        oq = make_double2(w.x + c * xq.x, w.y + c * xq.y);
+    };
+    // left: rows p' = c row_p - S row_q, q' = conj(S) row_p + c row_q
+    auto left = [](double c, double2 sx, double2 xp, double2 xq, double2& op, double2& oq) {
+        const double2 u = cmul(sx, xq), w = cmul(make_double2(sx.x, -sx.y), xp);
+        op = make_double2(c * xp.x - u.x, c * xp.y - u.y);
+        oq = make_double2(w.x + c * xq.x, w.y + c * xq.y);
+    };
+    const double2 zero = make_double2(0.0, 0.0);
+    auto update_block = [&](int k1, int k2, int r, int buf) {  // 2 x 2 block of A, in place
         int p1, q1, p2, q2;
         rr_pair(k1, r, np, p1, q1);
         rr_pair(k2, r, np, p2, q2);
-        const Rot r1 = rotation(a_in, n, p1, q1);
-        const Rot r2 = k2 == k1 ? r1 : rotation(a_in, n, p2, q2);
         const bool q1ok = q1 < n, q2ok = q2 < n;
-        auto ld = [&](int i, int j, bool ok) {
-            return ok ? a_in[static_cast<int64_t>(i) * n + j] : make_double2(0.0, 0.0);
-        };
-        const double2 app = ld(p1, p2, true), apq = ld(p1, q2, q2ok);
-        const double2 aqp = ld(q1, p2, q1ok), aqq = ld(q1, q2, q1ok && q2ok);
-        // right: [x_p, x_q] <- [c x_p - conj(S) x_q, S x_p + c x_q]
-        const double2 s2 = r2.s, s2c = make_double2(s2.x, -s2.y);
-        auto right = [&](double2 xp, double2 xq, double2& op, double2& oq) {
-            const double2 u = cmul(s2c, xq), w = cmul(s2, xp);
-            op = make_double2(r2.c * xp.x - u.x, r2.c * xp.y - u.y);
-            oq = make_double2(w.x + r2.c * xq.x, w.y + r2.c * xq.y);
-        };
-        double2 bpp, bpq, bqp, bqq;
-        right(app, apq, bpp, bpq);
-        right(aqp, aqq, bqp, bqq);
-        // left: rows p' = c row_p - S row_q, q' = conj(S) row_p + c row_q
-        const double2 s1 = r1.s, s1c = make_double2(s1.x, -s1.y);
-        auto left = [&](double2 xp, double2 xq, double2& op, double2& oq) {
-            const double2 u = cmul(s1, xq), w = cmul(s1c, xp);
-            op = make_double2(r1.c * xp.x - u.x, r1.c * xp.y - u.y);
-            oq = make_double2(w.x + r1.c * xq.x, w.y + r1.c * xq.y);
-        };
-        double2 cpp, cqp, cpq, cqq;
-        left(bpp, bqp, cpp, cqp);
-        left(bpq, bqq, cpq, cqq);
+        const double2 app = a[p1 * ld + p2], apq = q2ok ? a[p1 * ld + q2] : zero;
+        const double2 aqp = q1ok ? a[q1 * ld + p2] : zero;
+        const double2 aqq = q1ok && q2ok ? a[q1 * ld + q2] : zero;
+        double2 bpp, bpq, bqp, bqq, cpp, cqp, cpq, cqq;
+        right(rc[buf][k2], rs[buf][k2], app, apq, bpp, bpq);
+        right(rc[buf][k2], rs[buf][k2], aqp, aqq, bqp, bqq);
+        left(rc[buf][k1], rs[buf][k1], bpp, bqp, cpp, cqp);
+        left(rc[buf][k1], rs[buf][k1], bpq, bqq, cpq, cqq);
         if (k1 == k2) {  // the rotated pair: exact zeros off the diagonal, real diagonal
-            cpq = cqp = make_double2(0.0, 0.0);
+            cpq = cqp = zero;
             cpp.y = 0.0;
             cqq.y = 0.0;
         }
-        a_out[static_cast<int64_t>(p1) * n + p2] = cpp;
-        if (q2ok) a_out[static_cast<int64_t>(p1) * n + q2] = cpq;
-        if (q1ok) a_out[static_cast<int64_t>(q1) * n + p2] = cqp;
-        if (q1ok && q2ok) a_out[static_cast<int64_t>(q1) * n + q2] = cqq;
-        return;
+        a[p1 * ld + p2] = cpp;
+        if (q2ok) a[p1 * ld + q2] = cpq;
+        if (q1ok) a[q1 * ld + p2] = cqp;
+        if (q1ok && q2ok) a[q1 * ld + q2] = cqq;
+    };
+    // one of the half^2 <= NT blocks of A; column pair kv and every iv-th row of
+    // V for the threads of waves 1 and up
+    const int ta = tid / half, tb = tid % half;
+    auto update_a = [&](int r, int buf) {
+        if (ta < half) update_block(ta, tb, r, buf);
+    };
+    const int tv = (tid + NT - 64) % NT;
+    const int kv = tv % half, i0v = tv / half, iv = (NT - 64) / half;
+    auto update_v = [&](int r, int buf) {
+        int p, q;
+        rr_pair(kv, r, np, p, q);
+        if (q >= n || i0v >= iv) return;
+        const double c = rc[buf][kv];
+        const double2 sx = rs[buf][kv];
+        for (int i = i0v; i < n; i += iv) {
+            double2 op, oq;
+            right(c, sx, v[i * ld + p], v[i * ld + q], op, oq);
+            v[i * ld + p] = op;
+            v[i * ld + q] = oq;
+        }
+    };
+    double prev = -1.0;
+    int sweeps = 0;
+    for (; sweeps < max_sweeps && n > 1; ++sweeps) {
+        double off = 0.0, all = 0.0;
+        for (int e = tid; e < n * n; e += NT) {
+            const int i = e / n, j = e % n;
+            const double2 x = a[i * ld + j];
+            const double m2 = x.x * x.x + x.y * x.y;
+            all += m2;
+            if (i != j) off += m2;
+        }
+        for (int w = 32; w > 0; w >>= 1) {
+            off += __shfl_xor(off, w);
+            all += __shfl_xor(all, w);
+        }
+        if (lane == 0) {
+            s_red[wave] = off;
+            s_red[NW + wave] = all;
+        }
+        __syncthreads();
+        off = all = 0.0;
+        for (int w = 0; w < NW; ++w) {
+            off += s_red[w];
+            all += s_red[NW + w];
+        }
+        off = sqrt(off);
+        all = sqrt(all);
+        const bool stalled = sweeps >= 3 && prev >= 0.0 && off >= 0.25 * prev && off <= 1e-12 * all;
+        prev = off;
+        if (off <= tol * all || stalled) break;  // the same in every thread
+        if (wave == 0) rotations(0, 0);
+        for (int r = 0; r < np - 1; ++r) {
+            __syncthreads();  // the rotations of step r are there
+            update_a(r, r & 1);
+            __syncthreads();
+            if (wave > 0)
+                update_v(r, r & 1);
+            else if (r + 1 < np - 1)
+                rotations(r + 1, (r + 1) & 1);
+        }
+        __syncthreads();
     }
-    const int64_t tv = t - na_threads;
-    if (tv >= static_cast<int64_t>(n) * half) return;
-    const int i = static_cast<int>(tv / half), k = static_cast<int>(tv % half);
-    int p, q;
-    rr_pair(k, r, np, p, q);
-    const Rot ro = rotation(a_in, n, p, q);
-    const double2 xp = v_in[static_cast<int64_t>(i) * n + p];
-    if (q >= n) {
-        v_out[static_cast<int64_t>(i) * n + p] = xp;
-        return;
+    for (int e = tid; e < n * n; e += NT) {
+        const int i = e / n, j = e % n;
+        a_io[e] = a[i * ld + j];
+        v_io[e] = v[i * ld + j];
     }
-    const double2 xq = v_in[static_cast<int64_t>(i) * n + q];
-    const double2 sc = make_double2(ro.s.x, -ro.s.y);
-    const double2 u = cmul(sc, xq), w = cmul(ro.s, xp);
-    v_out[static_cast<int64_t>(i) * n + p] = make_double2(ro.c * xp.x - u.x, ro.c * xp.y - u.y);
-    v_out[static_cast<int64_t>(i) * n + q] = make_double2(w.x + ro.c * xq.x, w.y + ro.c * xq.y);
+    if (tid == 0) sweeps_out[blockIdx.x] = sweeps;
 }
 
 // ---------------------------------------------------------------- block Jacobi
@@ -581,8 +681,6 @@ __global__ __launch_bounds__(256) void jacobi_step_kernel(const double2* __restr
 // once per element step.  Entries past n are zero in S, so their rotations
 // are the identity and never couple them with the others; they are neither
 // read nor written.
-
-constexpr int kBJ = 16, kBP = 2 * kBJ, kBJMin = 64;
 
 struct Quad {  // a 2 x 2 block of complex entries
     double2 a00, a01, a10, a11;
@@ -1018,36 +1116,42 @@ size_t jacobi_work_bytes(int n, int batch) {
         const size_t qb = static_cast<size_t>(nbp / 2) * kBP * kBP * sizeof(double2) * batch;
         return ((qb + 255) & ~size_t(255)) + red;
     }
-    // second A and V buffers
-    const size_t nn = static_cast<size_t>(n) * n * batch * sizeof(double2);
-    return 2 * ((nn + 255) & ~size_t(255)) + red;
+    return (static_cast<size_t>(batch) * sizeof(double) + 255) & ~size_t(255);  // sweep counts
 }
 
 int jacobi_eigh(double2* a, double2* v, int n, int batch, double tol, int max_sweeps, void* work,
-                hipStream_t s) {
+                hipStream_t s, bool same_bits) {
     if (n <= 0 || batch <= 0) return 0;
+    if (n < kBJMin) {
+        double* count = static_cast<double*>(work);
+        const size_t lds = 2 * static_cast<size_t>(n) * (n | 1) * sizeof(double2);
+        // one thread per 2 x 2 block of A: 512 up to n = 44, 1,024 above
+        const int half = (n + 1) / 2, nt = half * half <= 512 ? 512 : 1024;
+        const auto kernel = nt == 512 ? (same_bits ? jacobi_lds_kernel<false, 512> : jacobi_lds_kernel<true, 512>)
+                                      : (same_bits ? jacobi_lds_kernel<false, 1024> : jacobi_lds_kernel<true, 1024>);
+        GW_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       static_cast<int>(lds)));
+        {
+            ProfScope ps("jacobi_sweep", s);
+            hipLaunchKernelGGL(kernel, dim3(batch), dim3(nt), lds, s, a, v, n, tol, max_sweeps, count);
+            GW_HIP_TRY(hipGetLastError());
+        }
+        std::vector<double> h(batch);
+        GW_HIP_TRY(hipMemcpyAsync(h.data(), count, h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+        GW_HIP_TRY(hipStreamSynchronize(s));
+        return static_cast<int>(*std::max_element(h.begin(), h.end()));
+    }
     const int64_t nn = static_cast<int64_t>(n) * n;
-    const bool blocked = n >= kBJMin;
     const int nblk = ceil_div(n, kBJ), nbp = nblk + (nblk & 1), npair = nbp / 2;
     const int64_t q_stride = static_cast<int64_t>(npair) * kBP * kBP;
-    const size_t first =
-        blocked ? ((static_cast<size_t>(q_stride) * batch * sizeof(double2) + 255) & ~size_t(255))
-                : 2 * ((static_cast<size_t>(nn) * batch * sizeof(double2) + 255) & ~size_t(255));
+    const size_t first = (static_cast<size_t>(q_stride) * batch * sizeof(double2) + 255) & ~size_t(255);
     char* w = static_cast<char*>(work);
     double* part = reinterpret_cast<double*>(w + first);
     double* res = part + static_cast<size_t>(batch) * kRedBlocks * 2;
     const unsigned eb = static_cast<unsigned>(std::min<int64_t>(ceil_div64(nn, 256), 4096));
     hipLaunchKernelGGL(eye_kernel, dim3(eb, 1, batch), dim3(256), 0, s, v, n, nn);
     GW_HIP_TRY(hipGetLastError());
-    if (n == 1) return 0;
-    // element sweeps: A and V ping-pong between the caller's buffers and the work area
-    const int np = n + (n & 1), half = np / 2;
-    const int64_t na_el = static_cast<int64_t>(half) * half;
-    const dim3 grid_el(static_cast<unsigned>(ceil_div64(na_el + static_cast<int64_t>(n) * half, 256)),
-                       1, batch);
-    const size_t nnb = (static_cast<size_t>(nn) * batch * sizeof(double2) + 255) & ~size_t(255);
-    double2 *ac = a, *an = reinterpret_cast<double2*>(w), *vc = v,
-            *vn = reinterpret_cast<double2*>(w + nnb);
     // block sweeps: in place, Q's in the work area
     double2* qs = reinterpret_cast<double2*>(w);
     const int na_bl = npair * (npair + 1) / 2;
@@ -1056,7 +1160,7 @@ int jacobi_eigh(double2* a, double2* v, int n, int batch, double tol, int max_sw
     std::vector<double> prev(batch, -1.0);
     int sweeps = 0;
     for (; sweeps < max_sweeps; ++sweeps) {
-        hipLaunchKernelGGL(offnorm_partial_kernel, dim3(kRedBlocks, 1, batch), dim3(256), 0, s, ac,
+        hipLaunchKernelGGL(offnorm_partial_kernel, dim3(kRedBlocks, 1, batch), dim3(256), 0, s, a,
                            n, nn, part);
         hipLaunchKernelGGL(offnorm_final_kernel, dim3(batch), dim3(256), 0, s, part, res);
         GW_HIP_TRY(hipGetLastError());
@@ -1076,28 +1180,13 @@ int jacobi_eigh(double2* a, double2* v, int n, int batch, double tol, int max_sw
         }
         if (done) break;
         ProfScope ps("jacobi_sweep", s);
-        if (blocked) {
-            for (int r = 0; r < nbp - 1; ++r) {
-                hipLaunchKernelGGL(bj_inner_kernel, dim3(npair, 1, batch), dim3(256), 0, s, ac, n,
-                                   nbp, r, qs, nn, q_stride);
-                hipLaunchKernelGGL(bj_update_kernel, dim3(na_bl + nv_bl, 1, batch), dim3(256), 0,
-                                   s, ac, vc, n, nbp, r, qs, nn, q_stride, na_bl);
-            }
-        } else {
-            for (int r = 0; r < np - 1; ++r) {
-                hipLaunchKernelGGL(jacobi_step_kernel, grid_el, dim3(256), 0, s, ac, an, vc, vn, n,
-                                   np, r, na_el, nn);
-                std::swap(ac, an);
-                std::swap(vc, vn);
-            }
+        for (int r = 0; r < nbp - 1; ++r) {
+            hipLaunchKernelGGL(bj_inner_kernel, dim3(npair, 1, batch), dim3(256), 0, s, a, n, nbp,
+                               r, qs, nn, q_stride);
+            hipLaunchKernelGGL(bj_update_kernel, dim3(na_bl + nv_bl, 1, batch), dim3(256), 0, s, a,
+                               v, n, nbp, r, qs, nn, q_stride, na_bl);
         }
         GW_HIP_TRY(hipGetLastError());
-    }
-    if (ac != a) {  // results back into the caller's buffers
-        GW_HIP_TRY(hipMemcpyAsync(a, ac, static_cast<size_t>(nn) * batch * sizeof(double2),
-                                  hipMemcpyDeviceToDevice, s));
-        GW_HIP_TRY(hipMemcpyAsync(v, vc, static_cast<size_t>(nn) * batch * sizeof(double2),
-                                  hipMemcpyDeviceToDevice, s));
     }
     return sweeps;
 }

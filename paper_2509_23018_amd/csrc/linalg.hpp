@@ -50,14 +50,18 @@ void launch_gather_cols(const double2* in, double2* out, int rows, int n_in, int
 
 // Eigen-decomposition of `batch` Hermitian n x n matrices (row-major, leading
 // dimension n, batch stride n*n) by cyclic two-sided Jacobi rotations in
-// parallel (round-robin) order, for n >= 64 grouped into blocks of 16 whose
-// pairs are rotated in LDS and applied as 32 x 32 unitaries: on return the
+// parallel (round-robin) order, below n = 64 by one workgroup per matrix in
+// LDS, from there grouped into blocks of 16 whose pairs are rotated in LDS and
+// applied as 32 x 32 unitaries: on return the
 // diagonal of a holds the eigenvalues, v (n x n, columns = eigenvectors)
 // satisfies A0 v = v diag(a).
 // `work` holds jacobi_work_bytes(n, batch) bytes.  Sweeps until the
 // off-diagonal Frobenius norm is below tol times the Frobenius norm, or
-// max_sweeps; returns the sweeps made (reads one scalar per sweep back: the
-// call waits for the stream).
+// max_sweeps; returns the sweeps made (reads them, or a scalar per block
+// sweep, back: the call waits for the stream).  same_bits keeps the longer form
+// of the rotation below n = 64: Diag feeds the eigenvectors to an
+// orthonormalisation that magnifies a changed last bit by the condition of its
+// block, 2e6.
 size_t jacobi_work_bytes(int n, int batch);
 
 // Inverse of the upper Cholesky factor of an n x n Hermitian positive
@@ -71,6 +75,6 @@ size_t jacobi_work_bytes(int n, int batch);
 size_t chol_work_bytes(int n);
 void chol_inverse(double2* g, double2* rinv, int n, void* work, hipStream_t s);
 int jacobi_eigh(double2* a, double2* v, int n, int batch, double tol, int max_sweeps, void* work,
-                hipStream_t s);
+                hipStream_t s, bool same_bits);
 
 }  // namespace gw

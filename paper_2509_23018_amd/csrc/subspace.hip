@@ -324,7 +324,7 @@ DiagResult run_subspace_basis(const double2* chi, int ng, int n_eig, double2* ba
         apply_a(pool[xi], pool[ti], 1.0);
         gemm(kOpC, kOpN, nb, nb, ng, one, pool[xi], nb, pool[ti], nb, g, nb);
         const double rr_tol = it == 0 ? 1e-6 : std::max(1e-15, std::min(1e-6, 1e-3 * res.residual));
-        res.sweeps += jacobi_eigh(g, u, nb, 1, rr_tol, 60, jw, s);
+        res.sweeps += jacobi_eigh(g, u, nb, 1, rr_tol, 60, jw, s, true);
         read_diag(g);
         std::iota(perm.begin(), perm.end(), 0);
         std::stable_sort(perm.begin(), perm.end(), [&](int a, int b) { return dg[a] > dg[b]; });

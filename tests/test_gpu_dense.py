@@ -106,3 +106,25 @@ def test_gpp_tiles_and_bands(nb, ns, ng, ne):
     assert bool((ws[need:] == 7).all())
     with pytest.raises(gw.GWError):
         gw.gw_gpp_sigma(*args, workspace=ws[:need - 256])
+
+
+# one workgroup per matrix below n = 64: no rotation, one, odd sizes (a phantom
+# index), the largest; diagonal, degenerate, rank-one, graded and zero matrices
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 16, 31, 47, 62, 63])
+def test_heev_one_workgroup(n):
+    rng = np.random.default_rng(n)
+    x = _crand(rng, n, n)
+    u = _crand(rng, n, 1)
+    g = np.logspace(0, -12, n)
+    a = np.stack([x + x.conj().T, np.diag(rng.standard_normal(n)).astype(complex), np.eye(n) + 0j,
+                  u @ u.conj().T, g[:, None] * (x + x.conj().T) * g[None, :],
+                  np.zeros((n, n), complex)])
+    w, v = (t.cpu().numpy() for t in gw.gw_heev(_to(a)))
+    for i in range(len(a)):
+        want = np.linalg.eigvalsh(a[i])
+        scale = np.abs(want).max()
+        # some ten sweeps of n - 1 steps, each within a few units of roundoff
+        tol = 10 * n * EPS
+        assert np.abs(w[i] - want).max() <= tol * scale
+        assert np.abs(v[i].conj().T @ v[i] - np.eye(n)).max() <= tol
+        assert np.abs(a[i] @ v[i] - v[i] * w[i][None, :]).max() <= tol * scale
