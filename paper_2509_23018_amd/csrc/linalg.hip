@@ -698,7 +698,14 @@ __device__ __forceinline__ int bj_row(int t, int bp, int bq) {  // local index -
 }
 
 // one pair's sweep; q_out[pair] = Q (32 x 32, row-major)
-__global__ __launch_bounds__(256) void bj_inner_kernel(const double2* __restrict__ a, int n,
+//
+// A chain of 31 dependent steps: the rotations (16 lanes of one wave), then the
+// update of S (waves 0 to 3, a 2 x 2 block per thread); waves 4 to 7 apply each
+// step's rotations to Q beside the next step's, off the chain.  41 us per
+// launch with one set of waves for all of it, 32 us so (n = 135), less with the
+// short rotation.
+template <bool SHORT>
+__global__ __launch_bounds__(512) void bj_inner_kernel(const double2* __restrict__ a, int n,
                                                        int nbp, int r,
                                                        double2* __restrict__ q_out,
                                                        int64_t a_stride, int64_t q_stride) {
@@ -708,69 +715,81 @@ __global__ __launch_bounds__(256) void bj_inner_kernel(const double2* __restrict
     const int bp = rr_index(blockIdx.x, r, nbp), bq = rr_index(nbp - 1 - blockIdx.x, r, nbp);
     __shared__ double2 sm[kBP][kBP + 1];
     __shared__ double2 qm[kBP][kBP + 1];
-    __shared__ double rc[kBP / 2];
-    __shared__ double2 rs[kBP / 2];
-    const int t = threadIdx.x;
-    for (int e = t; e < kBP * kBP; e += 256) {
+    __shared__ double rc[2][kBP / 2];
+    __shared__ double2 rs[2][kBP / 2];
+    for (int e = threadIdx.x; e < kBP * kBP; e += 512) {
         const int i = e / kBP, j = e % kBP;
         const int gi = bj_row(i, bp, bq), gj = bj_row(j, bp, bq);
         sm[i][j] = gi < n && gj < n ? a[static_cast<int64_t>(gi) * n + gj] : make_double2(0.0, 0.0);
         qm[i][j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
     }
     __syncthreads();
-    const int k1 = t / (kBP / 2), k2 = t % (kBP / 2);
+    const int t = threadIdx.x & 255, k1 = t / (kBP / 2), k2 = t % (kBP / 2);
+    const bool on_s = threadIdx.x < 256;
+    auto rotations = [&](int r2) {  // lanes 0 to 15 of wave 0
+        if (threadIdx.x >= kBP / 2) return;
+        int p, q;
+        rr_pair(t, r2, kBP, p, q);
+        const Rot ro = SHORT ? rotation_short(sm[p][p].x, sm[q][q].x, sm[p][q])
+                             : rotation_of(sm[p][p].x, sm[q][q].x, sm[p][q]);
+        rc[r2 & 1][t] = ro.c;
+        rs[r2 & 1][t] = ro.s;
+    };
+    rotations(0);
+    __syncthreads();
     for (int r2 = 0; r2 < kBP - 1; ++r2) {
-        if (t < kBP / 2) {
-            int p, q;
-            rr_pair(t, r2, kBP, p, q);
-            const Rot ro = rotation_of(sm[p][p].x, sm[q][q].x, sm[p][q]);
-            rc[t] = ro.c;
-            rs[t] = ro.s;
-        }
-        __syncthreads();
-        int p1, q1, p2, q2;
-        rr_pair(k1, r2, kBP, p1, q1);
+        int p2, q2;
         rr_pair(k2, r2, kBP, p2, q2);
-        const double c1 = rc[k1], c2 = rc[k2];
-        const double2 s1 = rs[k1], s2 = rs[k2];
-        const double2 s1c = make_double2(s1.x, -s1.y), s2c = make_double2(s2.x, -s2.y);
+        const double c2 = rc[r2 & 1][k2];
+        const double2 s2 = rs[r2 & 1][k2], s2c = make_double2(s2.x, -s2.y);
         // right: [x_p, x_q] <- [c x_p - conj(S) x_q, S x_p + c x_q]
         auto right = [&](double2 xp, double2 xq, double2& op, double2& oq) {
             const double2 u = cmul(s2c, xq), w = cmul(s2, xp);
             op = make_double2(c2 * xp.x - u.x, c2 * xp.y - u.y);
             oq = make_double2(w.x + c2 * xq.x, w.y + c2 * xq.y);
         };
-        // left: rows p' = c row_p - S row_q, q' = conj(S) row_p + c row_q
-        auto left = [&](double2 xp, double2 xq, double2& op, double2& oq) {
-            const double2 u = cmul(s1, xq), w = cmul(s1c, xp);
-            op = make_double2(c1 * xp.x - u.x, c1 * xp.y - u.y);
-            oq = make_double2(w.x + c1 * xq.x, w.y + c1 * xq.y);
-        };
-        double2 bpp, bpq, bqp, bqq, cpp, cpq, cqp, cqq;
-        right(sm[p1][p2], sm[p1][q2], bpp, bpq);
-        right(sm[q1][p2], sm[q1][q2], bqp, bqq);
-        left(bpp, bqp, cpp, cqp);
-        left(bpq, bqq, cpq, cqq);
-        if (k1 == k2) {  // the rotated pair: exact zeros off the diagonal, real diagonal
-            cpq = cqp = make_double2(0.0, 0.0);
-            cpp.y = 0.0;
-            cqq.y = 0.0;
+        if (on_s) {
+            int p1, q1;
+            rr_pair(k1, r2, kBP, p1, q1);
+            const double c1 = rc[r2 & 1][k1];
+            const double2 s1 = rs[r2 & 1][k1], s1c = make_double2(s1.x, -s1.y);
+            // left: rows p' = c row_p - S row_q, q' = conj(S) row_p + c row_q
+            auto left = [&](double2 xp, double2 xq, double2& op, double2& oq) {
+                const double2 u = cmul(s1, xq), w = cmul(s1c, xp);
+                op = make_double2(c1 * xp.x - u.x, c1 * xp.y - u.y);
+                oq = make_double2(w.x + c1 * xq.x, w.y + c1 * xq.y);
+            };
+            double2 bpp, bpq, bqp, bqq, cpp, cpq, cqp, cqq;
+            right(sm[p1][p2], sm[p1][q2], bpp, bpq);
+            right(sm[q1][p2], sm[q1][q2], bqp, bqq);
+            left(bpp, bqp, cpp, cqp);
+            left(bpq, bqq, cpq, cqq);
+            if (k1 == k2) {  // the rotated pair: exact zeros off the diagonal, real diagonal
+                cpq = cqp = make_double2(0.0, 0.0);
+                cpp.y = 0.0;
+                cqq.y = 0.0;
+            }
+            sm[p1][p2] = cpp;
+            sm[p1][q2] = cpq;
+            sm[q1][p2] = cqp;
+            sm[q1][q2] = cqq;
         }
-        sm[p1][p2] = cpp;
-        sm[p1][q2] = cpq;
-        sm[q1][p2] = cqp;
-        sm[q1][q2] = cqq;
-        // Q <- Q J on rows k1 and k1 + 16, columns (p2, q2)
-        for (int h = 0; h < 2; ++h) {
-            const int i = k1 + h * (kBP / 2);
-            double2 op, oq;
-            right(qm[i][p2], qm[i][q2], op, oq);
-            qm[i][p2] = op;
-            qm[i][q2] = oq;
+        __syncthreads();
+        if (on_s) {
+            if (r2 + 1 < kBP - 1) rotations(r2 + 1);
+        } else {
+            // Q <- Q J on rows k1 and k1 + 16, columns (p2, q2)
+            for (int h = 0; h < 2; ++h) {
+                const int i = k1 + h * (kBP / 2);
+                double2 op, oq;
+                right(qm[i][p2], qm[i][q2], op, oq);
+                qm[i][p2] = op;
+                qm[i][q2] = oq;
+            }
         }
         __syncthreads();
     }
-    for (int e = t; e < kBP * kBP; e += 256) q_out[e] = qm[e / kBP][e % kBP];
+    for (int e = threadIdx.x; e < kBP * kBP; e += 512) q_out[e] = qm[e / kBP][e % kBP];
 }
 
 // Workgroups [0, na): tiles (k, l), k <= l, of A, numbered row by row of the
@@ -1181,8 +1200,9 @@ int jacobi_eigh(double2* a, double2* v, int n, int batch, double tol, int max_sw
         if (done) break;
         ProfScope ps("jacobi_sweep", s);
         for (int r = 0; r < nbp - 1; ++r) {
-            hipLaunchKernelGGL(bj_inner_kernel, dim3(npair, 1, batch), dim3(256), 0, s, a, n, nbp,
-                               r, qs, nn, q_stride);
+            hipLaunchKernelGGL(same_bits ? bj_inner_kernel<false> : bj_inner_kernel<true>,
+                               dim3(npair, 1, batch), dim3(512), 0, s, a, n, nbp, r, qs, nn,
+                               q_stride);
             hipLaunchKernelGGL(bj_update_kernel, dim3(na_bl + nv_bl, 1, batch), dim3(256), 0, s, a,
                                v, n, nbp, r, qs, nn, q_stride, na_bl);
         }
