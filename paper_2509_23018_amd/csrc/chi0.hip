@@ -52,8 +52,9 @@ constexpr int kKt = 16;     // pairs per LDS stage
 // complex one on the 64x64 tile.  Pair rows past the chunk end (in the last
 // stage) are clamped and carry Delta = 0, columns past N_G are clamped and only
 // feed outputs that are not stored.
-// mode: 0 overwrite, 1 accumulate.  PART: store the whole T x T tile instead,
-// unmasked, row-major at cw (a partial sum over a range of pairs).
+// mode: bit 0 accumulate, bit 1 (T = 64) also write the conjugate transpose to
+// the mirrored tile.  PART: store the whole T x T tile instead, unmasked,
+// row-major at cw (a partial sum over a range of pairs).
 template <int T, int WI, int WJ, int PAD, bool PART = false>
 __device__ __forceinline__ void f64_tile(double2* lds, const double2* __restrict__ m, int64_t kc,
                                          int ng, const double2* __restrict__ dw,
@@ -265,14 +266,34 @@ __device__ __forceinline__ void f64_tile(double2* lds, const double2* __restrict
                 if (gi < ng && gj < ng) {
                     double2* p = cw + static_cast<int64_t>(gi) * ng + gj;
                     double2 v = make_double2(re, im);
-                    if (mode) {
+                    if (mode & 1) {
                         const double2 o = *p;
                         v.x += o.x;
                         v.y += o.y;
                     }
                     *p = v;
+                    // position li of row lj, permuted so that neither side of
+                    // the transposition meets its own banks
+                    if (T == 64 && (mode & 2)) lds[lj * T + (li ^ (lj & 7))] = v;
                 }
             }
+    if constexpr (T == 64 && !PART) {
+        if (mode & 2) {  // the mirrored tile, a row per wave at a time
+            __syncthreads();
+            for (int lj = wave; lj < T; lj += NT / 64) {
+                const int gj = j0 + lj, gi = i0 + lane;
+                if (gj >= ng || gi >= ng) continue;
+                const double2 v = lds[lj * T + (lane ^ (lj & 7))];
+                cw[static_cast<int64_t>(gj) * ng + gi] = make_double2(v.x, -v.y);
+            }
+        }
+    }
+}
+
+// Mode of a tile: the mirrored tile is written for Hermitian items off the
+// diagonal (a tile on it holds both halves).
+__device__ __forceinline__ int tile_mode(int mode, bool herm, int bi, int bj) {
+    return herm && bi != bj ? mode : mode & 1;
 }
 
 
@@ -290,9 +311,11 @@ __global__ __launch_bounds__(WI * WJ * 64) void chi0_f64_kernel(
     const int b = blockIdx.x;
     int w, bi, bj;
     if (b < n_main) {
-        item_tile(xcd_item(b, n_main), wl, nb, order, w, bi, bj);
+        const int t = xcd_item(b, n_main);
+        item_tile(t, wl, nb, order, w, bi, bj);
         f64_tile<T, WI, WJ, PAD>(lds, m, kc, ng, delta + static_cast<int64_t>(w) * kc,
-                                 chi + static_cast<int64_t>(w) * ng * ng, mode, bi, bj);
+                                 chi + static_cast<int64_t>(w) * ng * ng,
+                                 tile_mode(mode, hermitian_item(t, wl, nb), bi, bj), bi, bj);
         return;
     }
     const int u = b - n_main, j = u / parts, p = u % parts;
@@ -316,6 +339,7 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const double2* __restr
     const int j = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
     int w, bi, bj;
     item_tile(n_main + j, wl, nb, order, w, bi, bj);
+    mode = tile_mode(mode, hermitian_item(n_main + j, wl, nb), bi, bj);
     const int gi = bi * T + e / T, gj = bj * T + e % T;
     if (gi >= ng || gj >= ng) return;
     const double2* src = ws + static_cast<int64_t>(j) * parts * T * T + e;
@@ -325,13 +349,15 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const double2* __restr
         acc.x += v.x;
         acc.y += v.y;
     }
-    double2* dst = chi + static_cast<int64_t>(w) * ng * ng + static_cast<int64_t>(gi) * ng + gj;
-    if (mode) {
+    double2* cw = chi + static_cast<int64_t>(w) * ng * ng;
+    double2* dst = cw + static_cast<int64_t>(gi) * ng + gj;
+    if (mode & 1) {
         const double2 o = *dst;
         acc.x += o.x;
         acc.y += o.y;
     }
     *dst = acc;
+    if (mode & 2) cw[static_cast<int64_t>(gj) * ng + gi] = make_double2(acc.x, -acc.y);
 }
 
 // Persistent form for batches of problems: every workgroup takes items
@@ -353,8 +379,10 @@ __global__ __launch_bounds__(WI * WJ * 64) void chi0_f64_batched_kernel(
         const int4 itm = items[it];
         const QDesc d = qd[itm.x];
         f64_tile<T, WI, WJ, PAD>(lds, d.m, d.kc, d.ng, d.delta + static_cast<int64_t>(itm.y) * d.kc,
-                                 d.chi + static_cast<int64_t>(itm.y) * d.ng * d.ng, d.mode, itm.z,
-                                 itm.w);
+                                 d.chi + static_cast<int64_t>(itm.y) * d.ng * d.ng,
+                                 tile_mode(d.mode, (itm.z & kItemHermitian) != 0,
+                                           itm.z & ~kItemHermitian, itm.w),
+                                 itm.z & ~kItemHermitian, itm.w);
     }
 }
 
@@ -382,8 +410,11 @@ const Chi0Variant& chi0_variant_by_id(int id) {
 }
 
 // chi[i][j] = conj(chi[j][i]) for every (i, j) in a tile strictly below the
-// diagonal of tile x tile blocks (those the Hermitian contraction skipped).
-__global__ __launch_bounds__(256) void mirror_kernel(double2* __restrict__ chi, int ng, int tile) {
+// diagonal of tile x tile blocks (those the Hermitian contraction skipped),
+// for every Hermitian frequency of wl.
+__global__ __launch_bounds__(256) void mirror_kernel(double2* __restrict__ chi, int ng, int tile,
+                                                     WList wl) {
+    chi += static_cast<int64_t>(wl.w[blockIdx.z]) * ng * ng;
     const int j = blockIdx.x * 16 + (threadIdx.x & 15);
     const int i = blockIdx.y * 16 + (threadIdx.x >> 4);
     if (i >= ng || j >= ng) return;
@@ -450,8 +481,9 @@ size_t chi0_f64_tail_bytes() {
 
 void launch_chi0_f64(const double2* m, int64_t kc, int ng, const double2* delta,
                      const WList& wl, double2* chi, bool accumulate, hipStream_t s, int variant,
-                     double2* tail_ws) {
+                     double2* tail_ws, bool mirror) {
     if (kc <= 0 || wl.nh + wl.nf == 0) return;
+    if (mirror && !chi0_variant_mirrors(variant)) throw Error{-5, "this tile does not mirror"};
     const Chi0Variant& v = chi0_variant_by_id(variant);
     const int nb = ceil_div(ng, v.tile);
     const int64_t nitems = static_cast<int64_t>(wl.nh) * (nb * (nb + 1) / 2) +
@@ -474,7 +506,7 @@ void launch_chi0_f64(const double2* m, int64_t kc, int ng, const double2* delta,
             n_main = static_cast<int>(nitems) - rem;
         }
     }
-    int mode = accumulate ? 1 : 0;
+    int mode = (accumulate ? 1 : 0) | (mirror ? 2 : 0);
     const int* order = tile_order(nb);
     {
         ProfScope ps("chi0_f64", s);
@@ -507,6 +539,7 @@ void launch_chi0_f64_batched(const QDesc* qd, const int4* items, int nitems, int
 }
 
 int chi0_variant_tile(int variant) { return chi0_variant_by_id(variant).tile; }
+bool chi0_variant_mirrors(int variant) { return chi0_variant_tile(variant) == 64; }
 
 int chi0_f64_batched_blocks_per_cu(int variant) {
     const Chi0Variant& v = chi0_variant_by_id(variant);
@@ -525,10 +558,11 @@ int chi0_forced_variant() {
     return id;
 }
 
-void launch_mirror(double2* chi, int ng, int tile, hipStream_t s) {
+void launch_mirror(double2* chi, int ng, int tile, const WList& wl, hipStream_t s) {
+    if (wl.nh == 0 || ng <= tile) return;  // one tile holds both halves
     ProfScope ps("mirror", s);
-    hipLaunchKernelGGL(mirror_kernel, dim3(ceil_div(ng, 16), ceil_div(ng, 16)), dim3(256), 0, s,
-                       chi, ng, tile);
+    hipLaunchKernelGGL(mirror_kernel, dim3(ceil_div(ng, 16), ceil_div(ng, 16), wl.nh), dim3(256), 0,
+                       s, chi, ng, tile, wl);
     GW_HIP_TRY(hipGetLastError());
 }
 

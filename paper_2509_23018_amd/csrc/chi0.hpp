@@ -34,12 +34,15 @@ struct WList {
 // [kc][ng], delta [nz][kc], chi [nz][ng][ng].  variant selects the tile
 // shape (0: 64x64, 4 waves; 1: 128x128, 8 waves).  With tail_ws (device,
 // chi0_f64_tail_bytes() bytes) a last partial round of tiles is cut along the
-// pairs and reduced by a second launch; without it every tile is whole.
+// pairs and reduced by a second launch; without it every tile is whole.  With
+// mirror (where chi0_variant_mirrors) the tiles below the diagonal of the
+// Hermitian frequencies are written too.
 void launch_chi0_f64(const double2* m, int64_t kc, int ng, const double2* delta,
                      const WList& wl, double2* chi, bool accumulate, hipStream_t s, int variant,
-                     double2* tail_ws = nullptr);
+                     double2* tail_ws = nullptr, bool mirror = false);
 size_t chi0_f64_tail_bytes();  // for the current device
 int chi0_variant_tile(int variant);
+bool chi0_variant_mirrors(int variant);
 int chi0_f64_batched_blocks_per_cu(int variant);  // resident workgroups of the persistent kernel
 int chi0_forced_variant();  // GW_CHI0_VARIANT, or -1
 constexpr int kNumChi0Variants = 2;
@@ -51,8 +54,9 @@ struct QDesc {
     double2* chi;          // [nz][ng][ng]
     int64_t kc;
     int ng;
-    int mode;              // 0 overwrite, 1 accumulate
+    int mode;              // bit 0 accumulate, bit 1 mirror (Hermitian items)
 };
+constexpr int kItemHermitian = 1 << 30;  // flag in an item's tile row
 
 // Persistent contraction over items (problem, frequency, tile row, tile col);
 // counter must be 0 on entry.  grid = number of workgroups to keep resident.
@@ -118,8 +122,8 @@ constexpr int kSbTileI = 128, kSbTileJ = 64;  // split-BF16 workgroup tile
 inline int split_tile(int prec) { return prec == 2 || prec == 4 ? 128 : kSplitTile; }
 
 // Fill the tiles strictly below the diagonal (tile x tile blocks) from the
-// conjugate transpose.
-void launch_mirror(double2* chi, int ng, int tile, hipStream_t s);
+// conjugate transpose, for the Hermitian frequencies of wl.
+void launch_mirror(double2* chi, int ng, int tile, const WList& wl, hipStream_t s);
 
 void launch_fill_zero(double2* p, int64_t n, hipStream_t s);
 

@@ -659,6 +659,8 @@ void run_chi0(const gw_problem_t& pr, const Opts& o, hipStream_t s, char* base,
                                 s, v, tail_ws);
         });
     }
+    // the FP64 contraction of the last chunk mirrors its tiles as it writes them
+    const bool mirrors = o.precision == GW_FP64 && chi0_variant_mirrors(variant);
     for (size_t k = 0; k < chunks.size(); ++k) {
         const int b = static_cast<int>(k & 1);
         if (!two_streams && k > 0) produce(k);
@@ -671,7 +673,7 @@ void run_chi0(const gw_problem_t& pr, const Opts& o, hipStream_t s, char* base,
             const double2* mk_k = cmat(k);
             if (o.precision == GW_FP64)
                 launch_chi0_f64(mk_k, chunks[k].kc, L.ncols, dbuf[b], wl, chi, acc, s, variant,
-                                tail_ws);
+                                tail_ws, mirrors && k + 1 == chunks.size());
             else if (o.precision == GW_FP32)
                 launch_chi0_f32(mk_k, chunks[k].kc, L.ncols, dbuf[b], wl, chi, acc, s);
             else
@@ -680,10 +682,11 @@ void run_chi0(const gw_problem_t& pr, const Opts& o, hipStream_t s, char* base,
         }
         if (two_streams) GW_HIP_TRY(hipEventRecord(ax->ev[3 + b], s));
     }
-    for (int w = 0; w < pr.nz; ++w)
-        if (herm[w])
-            launch_mirror(chi + static_cast<int64_t>(w) * ng * ng, L.ncols,
-                          o.precision == GW_FP64 ? chi0_variant_tile(variant) : split_tile(o.precision), s);
+    if (!mirrors)
+        for (const WList& wl : wlists)
+            launch_mirror(chi, L.ncols,
+                          o.precision == GW_FP64 ? chi0_variant_tile(variant) : split_tile(o.precision),
+                          wl, s);
     mark_plan_used(*plan_ref, s);
 }
 
@@ -750,7 +753,8 @@ std::vector<int4> round_items(const BatchPlan& bp, int r, const gw_problem_t* pr
                         for (int j = sj; j < std::min(nb, sj + kSuper); ++j) {
                             if (b.herm[w] && j < i) continue;
                             if (!bp.split) {
-                                v.push_back({b.chunks[r].kc, make_int4(static_cast<int>(q), w, i, j)});
+                                const int f = b.herm[w] ? kItemHermitian : 0;
+                                v.push_back({b.chunks[r].kc, make_int4(static_cast<int>(q), w, i | f, j)});
                                 continue;
                             }
                             for (int h = 0; h < 2; ++h)  // the two 64-column halves
@@ -837,7 +841,9 @@ void upload_batch(const BatchPlan& bp, const gw_problem_t* probs, const Opts& o,
                 d.chi = reinterpret_cast<double2*>(probs[q].chi);
                 d.kc = kc;
                 d.ng = probs[q].ng;
-                d.mode = mode;
+                d.mode = mode;  // the last chunk's tiles are mirrored as they are written
+                if (chi0_variant_mirrors(bp.variant) && r + 1 == static_cast<int>(b.chunks.size()))
+                    d.mode |= 2;
                 desc.push_back(d);
             }
         }
@@ -913,12 +919,11 @@ void enqueue_batch(const BatchPlan& bp, const gw_problem_t* probs, const Opts& o
         GW_HIP_TRY(hipEventRecord(ax.ev[kEvUsed + b], s));
     }
     const int tile = bp.split ? kSbTileI : chi0_variant_tile(bp.variant);
-    for (int q = 0; q < nprob; ++q)
-        for (int w = 0; w < probs[q].nz; ++w)
-            if (bp.q[q].herm[w] && !bp.q[q].chunks.empty())
-                launch_mirror(reinterpret_cast<double2*>(probs[q].chi) +
-                                  static_cast<int64_t>(w) * probs[q].ng * probs[q].ng,
-                              probs[q].ng, tile, s);
+    if (bp.split || !chi0_variant_mirrors(bp.variant))
+        for (int q = 0; q < nprob; ++q)
+            if (!bp.q[q].chunks.empty())
+                for (const WList& wl : freq_lists(bp.q[q].herm))
+                    launch_mirror(reinterpret_cast<double2*>(probs[q].chi), probs[q].ng, tile, wl, s);
     for (int q = 0; q < nprob; ++q) mark_plan_used(*bp.q[q].plan, s);
 }
 

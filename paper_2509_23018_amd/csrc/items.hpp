@@ -24,6 +24,11 @@ __device__ __forceinline__ int xcd_item(int b, int n) {
     return x * q + (x < r ? x : r) + i;
 }
 
+// Whether item t is one of a Hermitian frequency.
+__device__ __forceinline__ bool hermitian_item(int t, const WList& wl, int nb) {
+    return t < wl.nh * (nb * (nb + 1) / 2);
+}
+
 // Frequency and tile of item t.  Items are frequency-major: every Hermitian
 // frequency over the tiles on or above the diagonal, then every other
 // frequency over all tiles.
