@@ -893,6 +893,9 @@ void run_chi0_backward(const MtxelPlan& plan, const gw_problem_t& p, const doubl
     std::vector<int64_t> moff(chunks.size(), 0);  // first row of chunk k in kept M
     for (size_t k = 1; k < chunks.size(); ++k)
         moff[k] = moff[k - 1] + static_cast<int64_t>(chunks[k - 1].vcount) * chunks[k - 1].cw;
+    // one chunk has nothing to overlap with: everything on s
+    const bool two_streams = chunks.size() > 1;
+    if (!two_streams) aux = s;
     auto produce = [&](size_t k) {
         const int b = static_cast<int>(k & 1);
         const BChunk& c = chunks[k];
@@ -914,7 +917,7 @@ void run_chi0_backward(const MtxelPlan& plan, const gw_problem_t& p, const doubl
                                dim3(256), 0, aux, p.e_v, p.e_c, pm, kc, za, w0, ddbufs[b]);
             GW_HIP_TRY(hipGetLastError());
         }
-        GW_HIP_TRY(hipEventRecord(ev[1 + b], aux));
+        if (two_streams) GW_HIP_TRY(hipEventRecord(ev[1 + b], aux));
     };
     if (L.sym_all) {
         ProfScope ps("bwd_sym", s);
@@ -925,14 +928,16 @@ void run_chi0_backward(const MtxelPlan& plan, const gw_problem_t& p, const doubl
                                    wsym + static_cast<int64_t>(w) * ng * ng);
         GW_HIP_TRY(hipGetLastError());
     }
-    GW_HIP_TRY(hipEventRecord(ev[0], s));
-    GW_HIP_TRY(hipStreamWaitEvent(aux, ev[0], 0));
+    if (two_streams) {
+        GW_HIP_TRY(hipEventRecord(ev[0], s));
+        GW_HIP_TRY(hipStreamWaitEvent(aux, ev[0], 0));
+    }
     produce(0);
     for (size_t ck = 0; ck < chunks.size(); ++ck) {
         {
             const int b = static_cast<int>(ck & 1);
             if (ck + 1 < chunks.size()) produce(ck + 1);
-            GW_HIP_TRY(hipStreamWaitEvent(s, ev[1 + b], 0));
+            if (two_streams) GW_HIP_TRY(hipStreamWaitEvent(s, ev[1 + b], 0));
             const int v0 = chunks[ck].v0, c0 = chunks[ck].c0;
             const int vcount = chunks[ck].vcount, cw = chunks[ck].cw;
             const int64_t kc = static_cast<int64_t>(vcount) * cw;
@@ -971,7 +976,7 @@ void run_chi0_backward(const MtxelPlan& plan, const gw_problem_t& p, const doubl
                 GW_HIP_TRY(hipGetLastError());
             }
             // M, Delta and dDelta of buffer b are not read after this point
-            GW_HIP_TRY(hipEventRecord(ev[3 + b], s));
+            if (two_streams) GW_HIP_TRY(hipEventRecord(ev[3 + b], s));
             if (!want_psi) continue;
             {
                 ProfScope ps("bwd_x", s);

@@ -178,8 +178,15 @@ void check_grid(const gw_grid_t* g) {
 void check_gvec(const int32_t* gvec, int ng, const int n[3]) {
     if (ng < 1) fail(GW_EINVAL, "ng must be >= 1");
     if (!gvec) fail(GW_EINVAL, "gvec is NULL");
+    // a bit per grid point finds repeats (6,031 G on 72^3: 47 KB cleared and
+    // 6,031 bits set, 15 us of every call where a hash set took 250);
+    // grids of more than 2^25 points, whose map would be the larger cost, keep
+    // the set
+    const int64_t nr = static_cast<int64_t>(n[0]) * n[1] * n[2];
+    const bool map = nr <= (int64_t(1) << 25);
+    std::vector<uint64_t> bits(map ? static_cast<size_t>(nr / 64 + 1) : 0, 0);
     std::unordered_set<int64_t> seen;
-    seen.reserve(static_cast<size_t>(ng) * 2);
+    if (!map) seen.reserve(static_cast<size_t>(ng) * 2);
     for (int i = 0; i < ng; ++i) {
         int64_t key = 0;
         for (int a = 0; a < 3; ++a) {
@@ -189,9 +196,18 @@ void check_gvec(const int32_t* gvec, int ng, const int n[3]) {
                 fail(GW_EINVAL, "gvec[" + std::to_string(i) + "][" + std::to_string(a) + "] = " +
                                     std::to_string(g) + " outside [" + std::to_string(lo) + ", " +
                                     std::to_string(hi) + "]");
-            key = key * 4096 + (g - lo);
+            key = key * n[a] + (g - lo);
         }
-        if (!seen.insert(key).second) fail(GW_EINVAL, "duplicate G at index " + std::to_string(i));
+        bool fresh;
+        if (map) {
+            uint64_t& word = bits[static_cast<size_t>(key >> 6)];
+            const uint64_t bit = uint64_t(1) << (key & 63);
+            fresh = !(word & bit);
+            word |= bit;
+        } else {
+            fresh = seen.insert(key).second;
+        }
+        if (!fresh) fail(GW_EINVAL, "duplicate G at index " + std::to_string(i));
     }
 }
 
@@ -513,6 +529,11 @@ Chi0Layout chi0_layout(const gw_problem_t& pr, const Opts& o, const MtxelPlan& p
     if (static_cast<int64_t>(pr.nv) * pr.nc == 0) return L;
     L.cs = chunk_shape(pr.nv, pr.nc, o.pair_chunk);
     L.kmax = static_cast<int64_t>(L.cs.vb) * L.cs.cw;
+    // one chunk has nothing to overlap with: one buffer, and everything on the
+    // caller's stream, without the four event calls between the two streams
+    // (16^3, 112 pairs: the call is bound by its host time, 70 us with them and
+    // 30 us without on one box)
+    if (L.cs.ncv * L.cs.ncc == 1) nbuf = L.nbuf = 1;
     const int64_t nw = L.ncols;
     Carver cv;
     for (int b = 0; b < nbuf; ++b) {
@@ -868,10 +889,13 @@ void enqueue_batch(const BatchPlan& bp, const gw_problem_t* probs, const Opts& o
                              static_cast<int64_t>(probs[q].ng) * probs[q].ng * probs[q].nz, s);
     if (bp.rounds == 0) return;
     launch_fill_zero(reinterpret_cast<double2*>(tab + bp.off_cnt), bp.rounds, s);
-    AuxCtx& ax = aux_ctx(s);
+    // a single round has nothing to overlap with: everything on s
+    const bool two_streams = bp.rounds > 1;
+    AuxCtx* ax = two_streams ? &aux_ctx(s) : nullptr;
     auto produce = [&](int r) {  // MTXEL + Delta of round r, every problem, companion stream
         const int b = r & 1;
-        if (r >= 2) GW_HIP_TRY(hipStreamWaitEvent(ax.aux, ax.ev[kEvUsed + b], 0));
+        const hipStream_t ps = two_streams ? ax->aux : s;
+        if (r >= 2) GW_HIP_TRY(hipStreamWaitEvent(ps, ax->ev[kEvUsed + b], 0));
         for (int q = 0; q < nprob; ++q) {
             const BatchQ& bq = bp.q[q];
             if (r >= static_cast<int>(bq.chunks.size())) continue;
@@ -880,19 +904,21 @@ void enqueue_batch(const BatchPlan& bp, const gw_problem_t* probs, const Opts& o
             launch_mtxel(*bq.plan, reinterpret_cast<const double2*>(pr.psi_v),
                          reinterpret_cast<const double2*>(pr.psi_c),
                          Rect{c.pm.v0, c.vcount, c.pm.c0, c.pm.cw}, pr.grid.volume, t2,
-                         reinterpret_cast<double2*>(base + bq.off_m[b]), ax.aux);
+                         reinterpret_cast<double2*>(base + bq.off_m[b]), ps);
             launch_delta(pr.e_v, pr.e_c, c.pm, c.kc, reinterpret_cast<const double2*>(pr.z), pr.nz,
-                         o.spin, reinterpret_cast<double2*>(base + bq.off_d[b]), ax.aux);
+                         o.spin, reinterpret_cast<double2*>(base + bq.off_d[b]), ps);
         }
-        GW_HIP_TRY(hipEventRecord(ax.ev[kEvMade + b], ax.aux));
+        if (two_streams) GW_HIP_TRY(hipEventRecord(ax->ev[kEvMade + b], ps));
     };
-    GW_HIP_TRY(hipEventRecord(ax.ev[kEvStart], s));
-    GW_HIP_TRY(hipStreamWaitEvent(ax.aux, ax.ev[kEvStart], 0));
+    if (two_streams) {
+        GW_HIP_TRY(hipEventRecord(ax->ev[kEvStart], s));
+        GW_HIP_TRY(hipStreamWaitEvent(ax->aux, ax->ev[kEvStart], 0));
+    }
     produce(0);
     for (int r = 0; r < bp.rounds; ++r) {
         const int b = r & 1;
         if (r + 1 < bp.rounds) produce(r + 1);
-        GW_HIP_TRY(hipStreamWaitEvent(s, ax.ev[kEvMade + b], 0));
+        if (two_streams) GW_HIP_TRY(hipStreamWaitEvent(s, ax->ev[kEvMade + b], 0));
         const int4* items = reinterpret_cast<const int4*>(tab + bp.off_items) + bp.item_off[r];
         int* counter = reinterpret_cast<int*>(tab + bp.off_cnt) + r;
         if (bp.split) {
@@ -916,7 +942,7 @@ void enqueue_batch(const BatchPlan& bp, const gw_problem_t* probs, const Opts& o
                 reinterpret_cast<const QDesc*>(tab + bp.off_desc) + static_cast<size_t>(r) * nprob,
                 items, bp.nitems[r], counter, s, bp.variant, bp.grid);
         }
-        GW_HIP_TRY(hipEventRecord(ax.ev[kEvUsed + b], s));
+        if (two_streams) GW_HIP_TRY(hipEventRecord(ax->ev[kEvUsed + b], s));
     }
     const int tile = bp.split ? kSbTileI : chi0_variant_tile(bp.variant);
     if (bp.split || !chi0_variant_mirrors(bp.variant))
