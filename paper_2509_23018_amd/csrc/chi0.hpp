@@ -80,9 +80,16 @@ constexpr int kSplitTile = 64;  // tile edge of the FP16-split and FP32 kernels
 // 128-wide square blocks); same scratch layout size as launch_chi0_split.
 // With tail_ws (device, sbf16_tail_bytes() bytes) a last partial round of
 // tiles is cut along the exponent blocks and reduced by a second launch.
-// variant: the LDS ring (0: the preferred stage height and depth for S; 1:
+// variant: the LDS ring (0: stages of two k-steps, of one at four slices; 1:
 // the other stage height), the same arithmetic in the same order.
 constexpr int kNumSplitVariants = 2;
+// The ring of a call that is not tuned: stages of one k-step.  Loads then come
+// in runs half as long, with one more stage between a load and its use.  Two
+// k-steps and one, 7,680 pairs on 48^3 (2,007 G, 4 frequencies, whole calls):
+// 2 slices 5,190 / 5,150 us, 3 slices 7,500 / 7,330, 4 slices 10,310 / 9,980,
+// 5 slices 13,220 / 13,180, 9-bit FP16 at 3 slices 8,470 / 8,200 and at 4
+// 11,050 / 11,000.
+constexpr int sbf16_default_variant(int S) { return S == 4 ? 0 : 1; }
 void launch_chi0_sbf16(int S, const double2* m, int64_t kc, int ng, const double2* delta, int nz,
                        const WList& wl, double2* chi, bool accumulate, void* scratch,
                        hipStream_t s, double2* tail_ws = nullptr, bool f16 = false,

@@ -256,8 +256,8 @@ __device__ __forceinline__ void wait_vm_lgkm0() {
 // address into padding), so "this step has landed" is vmcnt(loads per step)
 // after the next step's loads are in flight.
 // Stage geometry of the contraction for S slices and NW waves; RV picks the
-// ring (0: the preferred one below; 1: the other stage height, for the
-// autotuner).
+// ring (0: the one below; 1: the other stage height; sbf16_default_variant says
+// which a call takes that is not tuned).
 template <int S, int NW, int RV = 0>
 struct SbGeom {
     static constexpr int NT = NW * 64;

@@ -616,7 +616,7 @@ void run_chi0(const gw_problem_t& pr, const Opts& o, hipStream_t s, char* base,
     } else if (o.precision == GW_FP64 || split_ring) {
         variant = lookup_variant(tune_kind(o), L.ncols, chunks[0].kc);
         tune = variant < 0 && autotune_enabled(o);
-        if (variant < 0) variant = 0;
+        if (variant < 0) variant = split_ring ? sbf16_default_variant(o.n_slices) : 0;
     }
     const double2* z = reinterpret_cast<const double2*>(pr.z);
     const std::vector<bool> herm = hermitian_freqs(pr, o);
@@ -1004,7 +1004,7 @@ int batch_variant(const gw_problem_t* probs, int nprob, const Opts& o, hipStream
     const std::string kind = tune_kind(o);
     int v = lookup_variant(kind, pr.ng, ch[0].kc);
     if (v >= 0) return v;
-    if (!autotune_enabled(o)) return 0;
+    if (!autotune_enabled(o)) return split ? sbf16_default_variant(o.n_slices) : 0;
     const TuneLayout t = batch_tune_layout(probs, nprob, o);
     const PlanRef plan = get_plan(pr.grid.n, pr.gvec, pr.ng);
     launch_mtxel(*plan, reinterpret_cast<const double2*>(pr.psi_v),
