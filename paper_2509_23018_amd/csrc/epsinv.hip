@@ -48,22 +48,38 @@ __global__ __launch_bounds__(256) void build_eps_kernel(const double2* __restric
 // Matrices below are row-major n x n with leading dimension n, matrix w of the
 // batch at a + w * sa.
 
-// d[w] = A[w][K,K]^-1 for the bk x bk block at (k0, k0) (bk <= 64): scalar
-// Gauss-Jordan, no pivoting; d[w] at d + w * kB * kB, leading dimension kB.
+// Workgroup 0 of matrix w: d[w] = A[w][K,K]^-1 for the bk x bk block at
+// (k0, k0) (bk <= 64), scalar Gauss-Jordan without pivoting; d[w] at d +
+// w * kB * kB, leading dimension kB.  The others: L[w] = A[w][:, K] (rows in K
+// zero), then A[w][i, K] = 0 for the rows i not in K, which workgroup 0 does
+// not read; L[w] at l + w * n * kB, leading dimension kB.
 //
-// A chain of bk dependent steps on one workgroup, so the latency of a step is
-// the whole cost.  The block lives in registers (thread (ti, tj) holds rows
-// ti + 16 r and columns tj + 16 c); a step passes only the pivot row and
-// column through LDS, in two buffers, so it costs one barrier, one round of
+// The inverse is a chain of bk dependent steps on one workgroup, so the latency
+// of a step is the whole cost.  The block lives in registers (thread (ti, tj)
+// holds rows ti + 16 r and columns tj + 16 c); a step passes only the pivot row
+// and column through LDS, in two buffers, so it costs one barrier, one round of
 // LDS reads and one division.  Holding the block in LDS took four barriers and
 // three passes over it per step: 182 us for a 64 x 64 block against 42 us.
-__global__ __launch_bounds__(256) void block_inverse_kernel(const double2* __restrict__ a, int n,
-                                                            int64_t sa, int k0, int bk,
-                                                            double2* __restrict__ d) {
+// Two or four threads per 2 x 4 or 2 x 2 entries (47 and 50 us), and forming
+// only the next pivot's row and column before the barrier (42 us), did not help.
+__global__ __launch_bounds__(256) void pivot_kernel(double2* __restrict__ a, int n, int64_t sa,
+                                                    int k0, int bk, double2* __restrict__ d,
+                                                    double2* __restrict__ l) {
     constexpr int R = kB / 16;
     __shared__ double2 s_row[2][kB], s_col[2][kB];
-    const int64_t w = blockIdx.x;
-    const double2* aw = a + w * sa;
+    const int64_t w = blockIdx.y;
+    double2* aw = a + w * sa;
+    if (blockIdx.x > 0) {
+        const int64_t t = static_cast<int64_t>(blockIdx.x - 1) * 256 + threadIdx.x;
+        if (t >= static_cast<int64_t>(n) * bk) return;
+        const int i = static_cast<int>(t / bk), j = static_cast<int>(t % bk);
+        const bool in_k = i >= k0 && i < k0 + bk;
+        double2* src = aw + static_cast<int64_t>(i) * n + k0 + j;
+        l[w * static_cast<int64_t>(n) * kB + static_cast<int64_t>(i) * kB + j] =
+            in_k ? make_double2(0.0, 0.0) : *src;
+        if (!in_k) *src = make_double2(0.0, 0.0);
+        return;
+    }
     const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
     double2 x[R][R];
 #pragma unroll
@@ -120,6 +136,67 @@ __global__ __launch_bounds__(256) void block_inverse_kernel(const double2* __res
             const int i = ti + 16 * r, j = tj + 16 * c;
             if (i < bk && j < bk) d[w * kB * kB + i * kB + j] = x[r][c];
         }
+}
+
+// R[w] = D^-1 A[w][K, :] with R[w][:, K] = D^-1, to r + w * kB * n (leading
+// dimension n) and back into A[w][K, :], for blocks of at most 64 rows: one
+// workgroup per 16 columns, 4 waves of 16 x 16, three real MFMA products per
+// complex one.  Both operands fit LDS whole, so it is one load, one barrier
+// and 16 k-steps; the columns are read before they are overwritten.  On the
+// chain of an inverse, where each launch costs its latency (64 of these for
+// 2,007 G): 9 us at n = 512 against 5 + 5 us as a GEMM and a copy.
+__global__ __launch_bounds__(256) void pivot_rows_kernel(double2* __restrict__ a, int n, int64_t sa,
+                                                         int k0, int bk,
+                                                         const double2* __restrict__ d,
+                                                         double2* __restrict__ r) {
+    __shared__ double2 s_d[kB][kB + 1];  // [m][k]
+    __shared__ double2 s_a[kB][17];      // [k][n]
+    const int64_t w = blockIdx.y;
+    const int j0 = blockIdx.x * 16;
+    double2* aw = a + w * sa + static_cast<int64_t>(k0) * n;
+    const double2 zero = make_double2(0.0, 0.0);
+    double2 vd[16], va[4];  // every load in flight before the first is used
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = threadIdx.x + 256 * u, k = e / 16, j = j0 + e % 16;
+        va[u] = k < bk && j < n ? aw[static_cast<int64_t>(k) * n + j] : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int e = threadIdx.x + 256 * u, i = e / kB, k = e % kB;
+        vd[u] = i < bk && k < bk ? d[w * kB * kB + e] : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        s_a[e / 16][e % 16] = va[u];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        s_d[e / kB][e % kB] = vd[u];
+    }
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane & 15, kq = lane >> 4;
+    dbl4 p1 = zero4(), p2 = zero4(), p3 = zero4();
+#pragma unroll
+    for (int k = 0; k < kB; k += 4) {
+        const double2 b = s_a[k + kq][row], v = s_d[wave * 16 + row][k + kq];
+        p1 = mfma_f64(v.x, b.x, p1);
+        p2 = mfma_f64(v.y, b.y, p2);
+        p3 = mfma_f64(v.x + v.y, b.x + b.y, p3);
+    }
+    const int j = j0 + row;
+    const bool in_k = j >= k0 && j < k0 + bk;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int i = wave * 16 + 4 * t + kq;
+        if (i >= bk || j >= n) continue;
+        const double2 v = in_k ? s_d[i][j - k0]
+                               : make_double2(p1[t] - p2[t], p3[t] - p1[t] - p2[t]);
+        r[w * static_cast<int64_t>(kB) * n + static_cast<int64_t>(i) * n + j] = v;
+        aw[static_cast<int64_t>(i) * n + j] = v;
+    }
 }
 
 // L[w] = A[w][:, K] (rows in K zeroed), then A[w][i, K] = 0 for rows i not in
@@ -189,44 +266,44 @@ void gj_invert(double2* a, int n, int64_t sa, int nz, int kb, char* ws, hipStrea
     char* inner = ws + level_bytes(n, nz, kb);
     for (int k0 = 0; k0 < n; k0 += kb) {
         const int bk = std::min(kb, n - k0);
-        int64_t sd;
-        int ldd;
         if (kb == kB) {
-            hipLaunchKernelGGL(block_inverse_kernel, dim3(nz), dim3(256), 0, s, a, n, sa, k0, bk, d);
+            hipLaunchKernelGGL(pivot_kernel,
+                               dim3(static_cast<unsigned>(1 + ceil_div64(static_cast<int64_t>(n) * bk, 256)), nz),
+                               dim3(256), 0, s, a, n, sa, k0, bk, d, l);
             GW_HIP_TRY(hipGetLastError());
-            sd = kB * kB;
-            ldd = kB;
+            hipLaunchKernelGGL(pivot_rows_kernel, dim3(static_cast<unsigned>(ceil_div(n, 16)), nz),
+                               dim3(256), 0, s, a, n, sa, k0, bk, d, r);
+            GW_HIP_TRY(hipGetLastError());
         } else {
-            sd = static_cast<int64_t>(kb) * kb;
-            ldd = bk;
+            const int64_t sd = static_cast<int64_t>(kb) * kb;
             hipLaunchKernelGGL(copy_pivot_kernel, dim3(ceil_div(bk * bk, 256), 1, nz), dim3(256), 0,
                                s, a, n, sa, k0, bk, d, sd);
             GW_HIP_TRY(hipGetLastError());
             gj_invert(d, bk, sd, nz, kB, inner, s);
+            hipLaunchKernelGGL(take_panel_kernel,
+                               dim3(static_cast<unsigned>(ceil_div64(static_cast<int64_t>(n) * bk, 256)), 1, nz),
+                               dim3(256), 0, s, a, n, sa, k0, bk, kb, l);
+            GW_HIP_TRY(hipGetLastError());
+            ZGemm g1;  // R = D^-1 A[K, :]
+            g1.m = bk;
+            g1.n = n;
+            g1.k = bk;
+            g1.a = d;
+            g1.lda = bk;
+            g1.stride_a = sd;
+            g1.b = a + static_cast<int64_t>(k0) * n;
+            g1.ldb = n;
+            g1.stride_b = sa;
+            g1.c = r;
+            g1.ldc = n;
+            g1.stride_c = static_cast<int64_t>(kb) * n;
+            g1.batch = nz;
+            launch_zgemm(kOpN, kOpN, g1, s);
+            hipLaunchKernelGGL(put_rows_kernel,
+                               dim3(static_cast<unsigned>(ceil_div64(static_cast<int64_t>(bk) * n, 256)), 1, nz),
+                               dim3(256), 0, s, a, n, sa, k0, bk, kb, r, d, sd, bk);
+            GW_HIP_TRY(hipGetLastError());
         }
-        hipLaunchKernelGGL(take_panel_kernel,
-                           dim3(static_cast<unsigned>(ceil_div64(static_cast<int64_t>(n) * bk, 256)), 1, nz),
-                           dim3(256), 0, s, a, n, sa, k0, bk, kb, l);
-        GW_HIP_TRY(hipGetLastError());
-        ZGemm g1;  // R = D^-1 A[K, :]
-        g1.m = bk;
-        g1.n = n;
-        g1.k = bk;
-        g1.a = d;
-        g1.lda = ldd;
-        g1.stride_a = sd;
-        g1.b = a + static_cast<int64_t>(k0) * n;
-        g1.ldb = n;
-        g1.stride_b = sa;
-        g1.c = r;
-        g1.ldc = n;
-        g1.stride_c = static_cast<int64_t>(kb) * n;
-        g1.batch = nz;
-        launch_zgemm(kOpN, kOpN, g1, s);
-        hipLaunchKernelGGL(put_rows_kernel,
-                           dim3(static_cast<unsigned>(ceil_div64(static_cast<int64_t>(bk) * n, 256)), 1, nz),
-                           dim3(256), 0, s, a, n, sa, k0, bk, kb, r, d, sd, ldd);
-        GW_HIP_TRY(hipGetLastError());
         ZGemm g2;  // A -= L R
         g2.m = n;
         g2.n = n;
