@@ -702,9 +702,10 @@ __device__ __forceinline__ int bj_row(int t, int bp, int bq) {  // local index -
 // A chain of 31 dependent steps: the rotations (16 lanes of one wave), then the
 // update of S (waves 0 to 3, a 2 x 2 block per thread); waves 4 to 7 apply each
 // step's rotations to Q beside the next step's, off the chain.  41 us per
-// launch with one set of waves for all of it, 32 us so (n = 135), less with the
-// short rotation.
-template <bool SHORT>
+// launch with one set of waves for all of it, 32 us so (n = 135).  The long form
+// of the rotation for every caller: rotation_short's other roundings add up over
+// the sweeps in the phases of the eigenvectors (1e-12 apart at n = 90, 1e-7 at
+// 300, both equally good eigenvectors).
 __global__ __launch_bounds__(512) void bj_inner_kernel(const double2* __restrict__ a, int n,
                                                        int nbp, int r,
                                                        double2* __restrict__ q_out,
@@ -730,8 +731,7 @@ __global__ __launch_bounds__(512) void bj_inner_kernel(const double2* __restrict
         if (threadIdx.x >= kBP / 2) return;
         int p, q;
         rr_pair(t, r2, kBP, p, q);
-        const Rot ro = SHORT ? rotation_short(sm[p][p].x, sm[q][q].x, sm[p][q])
-                             : rotation_of(sm[p][p].x, sm[q][q].x, sm[p][q]);
+        const Rot ro = rotation_of(sm[p][p].x, sm[q][q].x, sm[p][q]);
         rc[r2 & 1][t] = ro.c;
         rs[r2 & 1][t] = ro.s;
     };
@@ -1200,9 +1200,8 @@ int jacobi_eigh(double2* a, double2* v, int n, int batch, double tol, int max_sw
         if (done) break;
         ProfScope ps("jacobi_sweep", s);
         for (int r = 0; r < nbp - 1; ++r) {
-            hipLaunchKernelGGL(same_bits ? bj_inner_kernel<false> : bj_inner_kernel<true>,
-                               dim3(npair, 1, batch), dim3(512), 0, s, a, n, nbp, r, qs, nn,
-                               q_stride);
+            hipLaunchKernelGGL(bj_inner_kernel, dim3(npair, 1, batch), dim3(512), 0, s, a, n, nbp, r,
+                               qs, nn, q_stride);
             hipLaunchKernelGGL(bj_update_kernel, dim3(na_bl + nv_bl, 1, batch), dim3(256), 0, s, a,
                                v, n, nbp, r, qs, nn, q_stride, na_bl);
         }

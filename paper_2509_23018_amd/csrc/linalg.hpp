@@ -59,7 +59,7 @@ void launch_gather_cols(const double2* in, double2* out, int rows, int n_in, int
 // off-diagonal Frobenius norm is below tol times the Frobenius norm, or
 // max_sweeps; returns the sweeps made (reads them, or a scalar per block
 // sweep, back: the call waits for the stream).  same_bits keeps the longer form
-// of the rotation: Diag feeds the eigenvectors to an orthonormalisation that
+// of the rotation below n = 64 too: Diag feeds the eigenvectors to an orthonormalisation that
 // magnifies a changed last bit by the condition of its block, 2e6.
 size_t jacobi_work_bytes(int n, int batch);
 
