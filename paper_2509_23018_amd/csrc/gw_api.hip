@@ -1416,8 +1416,10 @@ gw_status_t gw_mtxel(const gw_grid_t* grid, const gw_c128* psi_v, int32_t nv,
         hipStream_t s = static_cast<hipStream_t>(stream);
         const PlanRef plan = get_plan(grid->n, gvec, ng);
         // the linear pair range as rectangles of at most kBatch pairs: partial
-        // rows alone, whole rows in blocks of up to 4 valence bands (the MTXEL
-        // tile height) cut into column ranges, written with row stride nc
+        // rows alone, whole rows in blocks of up to 8 valence bands (two MTXEL
+        // tiles, which read the same conduction bands: 48^3, 8 x 480 pairs 0.90 ms
+        // in blocks of 4, 0.85 in blocks of 8) cut into column ranges, written with
+        // row stride nc
         constexpr int64_t kBatch = 4096;
         struct Piece {
             Rect r;
@@ -1434,7 +1436,7 @@ gw_status_t gw_mtxel(const gw_grid_t* grid, const gw_c128* psi_v, int32_t nv,
                 p0 += cnt;
                 continue;
             }
-            const int vb = static_cast<int>(std::min<int64_t>((pend - p0) / nc, 4));
+            const int vb = static_cast<int>(std::min<int64_t>((pend - p0) / nc, 8));
             const int cw = static_cast<int>(std::min<int64_t>(nc, kBatch / vb));
             for (int c0 = 0; c0 < nc; c0 += cw)
                 rects.push_back({Rect{v, vb, c0, std::min(cw, nc - c0)}, p0 - pair_begin + c0});

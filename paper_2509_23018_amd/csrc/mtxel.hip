@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "items.hpp"
 #include "plan.hpp"
 #include "lifetime.hpp"
 #include "prof.hpp"
@@ -65,12 +66,29 @@ constexpr int kSlab = 16;  // j3 values per LDS slab (4 MFMA k-steps)
 // row rotation by 8, two 32-bit moves.
 __device__ __forceinline__ double row_swap8(double v) {
     const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(v));
-    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b & 0xffffffffull), 0x128, 0xf,
-                                               0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), 0x128, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b & 0xffffffffull), 0x128, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), 0x128, 0xf, 0xf, true);
     return __longlong_as_double(static_cast<long long>(
         (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) |
         static_cast<unsigned>(lo)));
+}
+
+// The value of the lane 4 further in this lane's 16-lane row (lanes 12-15 take
+// the first four's): a DPP row rotation.
+__device__ __forceinline__ double row_next4(double v) {
+    const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(v));
+    const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b & 0xffffffffull), 0x12c, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), 0x12c, 0xf, 0xf, true);
+    return __longlong_as_double(static_cast<long long>(
+        (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) |
+        static_cast<unsigned>(lo)));
+}
+
+// Four independent blocks D_b += A_b B_b of 4 x 4 x 4: lane l supplies
+// A_b[l%4][l/16] and B_b[l/16][l%4] of block b = l/4%4 and receives
+// D_b[l/16][l%4] (measured on gfx950).
+__device__ __forceinline__ double mfma_f64_4(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
 // The slab ring is written by global_load_lds and read with ds_read, and the
@@ -254,7 +272,7 @@ __global__ __launch_bounds__(kZyThreads) void mtxel_zy_kernel(
                 for (int b3 = 0; b3 < NB3; ++b3) a2r[p][b2][b3] = a2i[p][b2][b3] = zero4();
         }
     };
-    constexpr bool kPack = PPW % 2 == 0;
+    constexpr bool kPack = false;
     const bool half_last = (n2 & 15) != 0 && (n2 & 15) <= 8;  // last j2 block at most 8 rows
     int pending = -1;  // plane whose T2 is complete and not yet stored
     int cur = 0, fill = ring - 1;  // ring slots: contracted, refilled next
@@ -362,6 +380,289 @@ __global__ __launch_bounds__(kZyThreads) void mtxel_zy_kernel(
     wait_vmcnt<0>();  // no load into this workgroup's LDS may outlive it
 }
 
+// ---------------------------------------------------------------- kernel 1, folded
+
+// The same product and stages for boxes of at most 16 classes on the y and z
+// axes, on folded lines and the 4x4x4 FP64 MFMA (four independent 4 x 4 x 4
+// blocks; the same flops per cycle as 16x16x4).
+//
+// Folding.  With c = (N - 1)/2 the points of a line pair up as c +- u, and
+//     X(k) = e^{2 pi i k c/N} sum_u [cos(2 pi k u/N) e_u + i sin(2 pi k u/N) o_u],
+//     e_u = x(c + u) + x(c - u),  o_u = x(c + u) - x(c - u),
+// over the H = ceil(N/2) pairs (u = 1/2, 3/2, ... for even N; 0, 1, ... for odd
+// N, where the centre meets itself and its cosine is halved).  So each sum runs
+// over half the line, half the work of the unfolded one; the leading phase,
+// the same for a whole frequency, is left to the x stage.  The cosines
+// multiply e and the sines o: two operands, which a 16-wide MFMA could only
+// share by leaving half its columns empty when a box has 8 classes (48^3).
+// The 4-wide blocks take any multiple of 4 classes.
+//
+// Stage z: a slab holds, of each band, 8 row pairs of j2 (rows 0-7: c + u, rows
+// 8-15: c - u) by 8 column pairs of j3.  A lane forms rho at both columns of a
+// pair for its row; A = the 16 rows (block b: rows 4 b .. 4 b + 3), B = 4
+// classes, the same in every block.  Its output, lane (class j, block b, row i
+// of the block), is at once the B operand of
+// Stage y: K = the 4 rows of a block.  The rows are folded first (the partner
+// of a row is 8 lanes away), after which blocks 0 and 1 hold e, 2 and 3 o; A =
+// the cosines of 4 k2 classes in blocks 0 and 1, the sines in 2 and 3.  A
+// block's sum covers its own rows: C = blocks 0 + 1 and S = blocks 2 + 3, added
+// once per plane.
+//
+// Per band pair and block of 16 rows: 4 C3 MFMAs of 16 cycles and 10 FP64
+// instructions for every 4 column pairs, and 4 C2 C3 MFMAs of stage y.  At 48^3
+// (8 x 8 classes, 3,840 pairs) the products alone take 0.55 ms of the first
+// version's 0.79, with the T2 stores 0.61, with the loads 0.72: bound by the FP64
+// pipes and by the slabs' arrival together, so the loads' order counts.  The next
+// slab's loads are placed between the products (as a burst they hold up this
+// slab's reads behind them; 0.79 -> 0.73 ms), DPP moves without a cleared
+// destination (0.70), and an XCD runs the valence tiles of a conduction tile side
+// by side (8 valence bands of one launch: 0.69 ms, 0.91 unfolded; 72^3, 12 x 12
+// classes: 3.77 ms, 5.57 unfolded).  Slower: a ring of 4 slabs (more in flight
+// than L2 holds; 1 to 8 %), and reading the next slab's first operands ahead of
+// its barrier, which leaves a slab less time to land (15 %).
+template <int C2, int C3, int PPW>
+__global__ __launch_bounds__(kZyThreads) void mtxel_fold_kernel(
+    const double2* __restrict__ psi_v, const double2* __restrict__ psi_c, int64_t nr, Rect rc,
+    int n1, int planes_per_group, int n2, int n3, const double2* __restrict__ w3f,
+    const double* __restrict__ w2f, const int2* __restrict__ boxf4, int n23,
+    double2* __restrict__ t2, int ring, int gx, int gy) {
+    constexpr int TV = 4, TC = 2 * PPW, NBANDS = TV + TC;
+    constexpr int NSLAB = NBANDS * 256;        // 16-byte entries per slab
+    constexpr int NFILL = NSLAB / kZyThreads;  // loads per thread per slab
+    static_assert(NSLAB % kZyThreads == 0, "slab fill");
+    extern __shared__ double2 lds[];
+    const int h2 = (n2 + 1) / 2, h3 = (n3 + 1) / 2;
+    const int nslab = (h3 + 7) / 8, nrb = (h2 + 7) / 8, nks = (h3 + 3) / 4;
+    const int w3n = nks * C3 * 16, w2n = nrb * C2 * 64;
+    constexpr int boxn = C2 * 8 * C3 * 4;
+    double2* s_w3 = lds;                                             // [k-step][group][k][class]
+    double* s_w2 = reinterpret_cast<double*>(lds + w3n);             // [row block][group][lane]
+    int2* s_box = reinterpret_cast<int2*>(lds + w3n + w2n / 2);      // [k2 class, sign][k3 class]
+    double2* s_ring = lds + w3n + w2n / 2 + boxn / 2;                // [ring][NBANDS][16][16]
+    for (int i = threadIdx.x; i < w3n; i += kZyThreads) s_w3[i] = w3f[i];
+    for (int i = threadIdx.x; i < w2n; i += kZyThreads) s_w2[i] = w2f[i];
+    for (int i = threadIdx.x; i < boxn; i += kZyThreads) s_box[i] = boxf4[i];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, row = lane & 15, kq = lane >> 4;
+    const int cls = lane & 3, blk = (lane >> 2) & 3;
+    const double fold = blk < 2 ? 1.0 : -1.0;
+    // tile of this workgroup: each XCD takes a contiguous run, valence tiles
+    // fastest, so the tiles that read the same conduction bands share one L2
+    int t = xcd_item(blockIdx.x, gridDim.x);
+    const int y = t % gy;
+    t /= gy;
+    const int x = t % gx, z = t / gx;
+    const int tv0 = y * TV, tc0 = x * TC;
+
+    // staging entries of this thread: e = u * 512 + tid -> band e / 256 (the same
+    // for a wave: scalar bases), row (e >> 4) & 15, column (e & 15) ^ row, the
+    // same for every u; j2 and j3 at row block and slab 0, going up (c + u) or
+    // down; bands, rows and columns clamped
+    static_assert(TV == 4, "entries u < 2 are the valence bands");
+    const double2* fptr[NFILL];
+#pragma unroll
+    for (int u = 0; u < NFILL; ++u) {
+        const int fb = 2 * u + (wave >> 2);
+        if (u < 2)
+            fptr[u] = psi_v + static_cast<int64_t>(rc.v0 + min(tv0 + fb, rc.nv - 1)) * nr;
+        else
+            fptr[u] = psi_c + static_cast<int64_t>(rc.c0 + min(tc0 + fb - TV, rc.nc - 1)) * nr;
+    }
+    const int fr = (tid >> 4) & 15, fc = (tid & 15) ^ fr;
+    const bool up2 = fr < 8, up3 = fc < 8;
+    const int f2 = up2 ? n2 / 2 + fr : (n2 + 1) / 2 - 1 - (fr - 8);
+    const int f3 = up3 ? n3 / 2 + fc : (n3 + 1) / 2 - 1 - (fc - 8);
+    struct Fill {
+        int64_t plane;
+        unsigned off;
+        int slot;
+    };
+    auto fill_at = [&](int j1, int rb, int sl, int slot) {
+        const int j2 = up2 ? min(f2 + 8 * rb, n2 - 1) : max(f2 - 8 * rb, 0);
+        const int j3 = up3 ? min(f3 + 8 * sl, n3 - 1) : max(f3 - 8 * sl, 0);
+        return Fill{static_cast<int64_t>(j1) * n2 * n3, static_cast<unsigned>(j2 * n3 + j3),
+                    slot * NSLAB + wave * 64};
+    };
+    auto fill_one = [&](const Fill& f, int u) {
+        const double2* src[1] = {fptr[u] + f.plane + f.off};
+        ring_fill<1>(s_ring, f.slot + u * kZyThreads, src);
+    };
+    // slab entry of (band, row, column)
+    auto sent = [&](int band, int r, int c) { return band * 256 + r * 16 + (c ^ r); };
+
+    const int vl = wave >> 1, cl0 = (wave & 1) * PPW;
+    bool pok[PPW];
+#pragma unroll
+    for (int p = 0; p < PPW; ++p) pok[p] = tv0 + vl < rc.nv && tc0 + cl0 + p < rc.nc;
+
+    // sums: [0] Re, [1] Im of the cosines, [2], [3] of the sines of stage z
+    double a1[PPW][C3][4], a2[PPW][C2][C3][4];
+#pragma unroll
+    for (int p = 0; p < PPW; ++p)
+#pragma unroll
+        for (int g3 = 0; g3 < C3; ++g3)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a1[p][g3][q] = 0.0;
+#pragma unroll
+                for (int g2 = 0; g2 < C2; ++g2) a2[p][g2][g3][q] = 0.0;
+            }
+
+    // this workgroup's planes: j1 in [j1b, j1e)
+    const int j1b = z * planes_per_group;
+    const int j1e = min(n1, j1b + planes_per_group);
+    const int total = (j1e - j1b) * nrb * nslab;
+    int j1 = j1b, rb = 0, sl = 0;       // position being contracted
+    int nj1 = j1b, nrw = 0, nsl = 0;    // next position to load (clamped at the last slab)
+    auto advance = [&](int& a, int& b, int& c) {
+        if (++c == nslab) {
+            c = 0;
+            if (++b == nrb) {
+                b = 0;
+                if (++a == j1e) {
+                    a = j1e - 1;
+                    b = nrb - 1;
+                    c = nslab - 1;
+                }
+            }
+        }
+    };
+    __syncthreads();  // tables visible
+    for (int i = 0; i < ring - 1; ++i) {
+        const Fill nf = fill_at(nj1, nrw, nsl, i);
+#pragma unroll
+        for (int u = 0; u < NFILL; ++u) fill_one(nf, u);
+        advance(nj1, nrw, nsl);
+    }
+    // T2 of plane pj1.  A lane of block 0 (2) then holds the whole C (S) of its
+    // classes and, 8 lanes away, the S (C); C + i S is T2 at k2 = +a, and in
+    // block 2 S + i C = i (C - i S), i times T2 at k2 = -a (the x stage takes
+    // the i out again).  The z sums pair up the same way within a lane.
+    auto store_plane = [&](int pj1) {
+#pragma unroll
+        for (int p = 0; p < PPW; ++p) {
+            const int64_t k = static_cast<int64_t>(tv0 + vl) * rc.nc + tc0 + cl0 + p;
+            double2* o = t2 + (k * n1 + pj1) * n23;
+#pragma unroll
+            for (int g2 = 0; g2 < C2; ++g2)
+#pragma unroll
+                for (int g3 = 0; g3 < C3; ++g3) {
+                    double s[4], x[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        s[q] = a2[p][g2][g3][q] + row_next4(a2[p][g2][g3][q]);
+                        x[q] = row_swap8(s[q]);
+                        a2[p][g2][g3][q] = 0.0;
+                    }
+                    const double cr = s[0] - x[1], ci = s[1] + x[0];
+                    const double sr = s[2] - x[3], si = s[3] + x[2];
+                    if (pok[p] && (blk & 1) == 0) {
+                        const int2 d = s_box[((g2 * 4 + kq) * 2 + (blk >> 1)) * (C3 * 4) + g3 * 4 + cls];
+                        if (d.x >= 0) o[d.x] = make_double2(cr - si, ci + sr);
+                        if (d.y >= 0) o[d.y] = make_double2(cr + si, ci - sr);
+                    }
+                }
+        }
+    };
+    int pending = -1;              // plane whose T2 is complete and not yet stored
+    int cur = 0, fill = ring - 1;  // ring slots: contracted, refilled next
+    for (int it = 0;; ++it) {
+        // as in mtxel_zy_kernel: this slab has landed in every wave, and every
+        // wave is done with the slot the next load refills
+        if (ring == 3)
+            wait_vmcnt<NFILL>();
+        else
+            wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");  // keep the LDS reads below the barrier
+        if (pending >= 0) {  // a slab before the next y stage: a2 is free again in time
+            store_plane(pending);
+            pending = -1;
+        }
+        if (it == total) break;
+        // the next slab's loads go out one by one between the products of the
+        // first k-step: as a burst they hold up this slab's reads behind them
+        const Fill nf = fill_at(nj1, nrw, nsl, fill);
+        advance(nj1, nrw, nsl);
+        const int slab = cur * NSLAB;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int ks = sl * 2 + kk;
+            if (ks >= nks) break;  // uniform
+            const int c = 4 * kk + kq;
+            const double2 vp = ring_read(s_ring, slab + sent(vl, row, c));
+            const double2 vm = ring_read(s_ring, slab + sent(vl, row, c + 8));
+            double2 w[C3];
+#pragma unroll
+            for (int g3 = 0; g3 < C3; ++g3) w[g3] = s_w3[(ks * C3 + g3) * 16 + kq * 4 + cls];
+            // one pair's values are read while the one before is multiplied
+            double2 cpn = ring_read(s_ring, slab + sent(TV + cl0, row, c));
+            double2 cmn = ring_read(s_ring, slab + sent(TV + cl0, row, c + 8));
+#pragma unroll
+            for (int p = 0; p < PPW; ++p) {
+                const double2 cp = cpn, cm = cmn;
+                if (p + 1 < PPW) {
+                    cpn = ring_read(s_ring, slab + sent(TV + cl0 + p + 1, row, c));
+                    cmn = ring_read(s_ring, slab + sent(TV + cl0 + p + 1, row, c + 8));
+                }
+                const double2 r = cmul_conj_a(vp, cp);
+                const double er = fma(vm.x, cm.x, fma(vm.y, cm.y, r.x));
+                const double ei = fma(vm.x, cm.y, fma(-vm.y, cm.x, r.y));
+                const double orr = fma(2.0, r.x, -er), oi = fma(2.0, r.y, -ei);
+#pragma unroll
+                for (int g3 = 0; g3 < C3; ++g3) {
+                    a1[p][g3][0] = mfma_f64_4(er, w[g3].x, a1[p][g3][0]);
+                    a1[p][g3][1] = mfma_f64_4(ei, w[g3].x, a1[p][g3][1]);
+                    a1[p][g3][2] = mfma_f64_4(orr, w[g3].y, a1[p][g3][2]);
+                    a1[p][g3][3] = mfma_f64_4(oi, w[g3].y, a1[p][g3][3]);
+                    if (kk == 0) {
+                        constexpr int Q = PPW * C3;
+                        const int i = p * C3 + g3;
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = i * NFILL / Q; u < (i + 1) * NFILL / Q; ++u) fill_one(nf, u);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (sl == nslab - 1) {
+            // stage y of this row block
+#pragma unroll
+            for (int p = 0; p < PPW; ++p) {
+                double w[C2];
+#pragma unroll
+                for (int g2 = 0; g2 < C2; ++g2) w[g2] = s_w2[(rb * C2 + g2) * 64 + lane];
+#pragma unroll
+                for (int g3 = 0; g3 < C3; ++g3)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const double y = fma(fold, a1[p][g3][q], row_swap8(a1[p][g3][q]));
+#pragma unroll
+                        for (int g2 = 0; g2 < C2; ++g2)
+                            a2[p][g2][g3][q] = mfma_f64_4(w[g2], y, a2[p][g2][g3][q]);
+                        a1[p][g3][q] = 0.0;
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (rb == nrb - 1) pending = j1;  // stored after the next barrier
+        }
+        if (++sl == nslab) {
+            sl = 0;
+            if (++rb == nrb) {
+                rb = 0;
+                ++j1;
+            }
+        }
+        cur = cur + 1 == ring ? 0 : cur + 1;
+        fill = fill + 1 == ring ? 0 : fill + 1;
+    }
+    wait_vmcnt<0>();  // no load into this workgroup's LDS may outlive it
+}
+
 // ---------------------------------------------------------------- kernel 2
 
 // M_box[k1][d] = sum_j1 W1[k1][j1] T2[j1][d] on MFMA: A = the real cos | sin
@@ -372,11 +673,13 @@ __global__ __launch_bounds__(kZyThreads) void mtxel_zy_kernel(
 // scattered to the G list.
 // Pair k of the launch (k0 + blockIdx.x in the rectangle's row-major order,
 // cw pairs per valence row) is written to output row (k / cw) * ldm + k % cw.
+// ph (NULL: none): a phase per disc index that the values of T2 still lack.
 template <int NB1>
 __global__ __launch_bounds__(kThreads) void mtxel_x_kernel(
     const double2* __restrict__ t2, int n1, int n1p, int n23, int n23p,
     const double* __restrict__ w1re, const int* __restrict__ gmapf, int ng, double dv,
-    int64_t npairs, int64_t k0, int cw, int64_t ldm, double2* __restrict__ m_out) {
+    int64_t npairs, int64_t k0, int cw, int64_t ldm, double2* __restrict__ m_out,
+    const double2* __restrict__ ph) {
     extern __shared__ double2 lds_x[];
     double* s_w1 = reinterpret_cast<double*>(lds_x);
     const int q1 = n1p >> 2;
@@ -395,6 +698,11 @@ __global__ __launch_bounds__(kThreads) void mtxel_x_kernel(
         for (int b = 0; b < NB1; ++b) ar[b] = ai[b] = zero4();
         const int d = db * 16 + row;
         const bool dok = d < n23;
+        double2 f = make_double2(dv, 0.0);
+        if (ph) {
+            f = ph[d];
+            f = make_double2(dv * f.x, dv * f.y);
+        }
         for (int ks0 = 0; ks0 < q1; ks0 += kLoadBatch) {
             double2 xb[kLoadBatch];
 #pragma unroll
@@ -423,8 +731,8 @@ __global__ __launch_bounds__(kThreads) void mtxel_x_kernel(
                 const double cr = ar[b][t], ci = ai[b][t], sr = ar[b][t + 2], si = ai[b][t + 2];
                 const int e = ((b * 8 + 4 * t + kq) * 2) * n23p + d;
                 const int gp = gmapf[e], gm = gmapf[e + n23p];
-                if (gp >= 0) dst[gp] = make_double2(dv * (cr - si), dv * (ci + sr));
-                if (gm >= 0) dst[gm] = make_double2(dv * (cr + si), dv * (ci - sr));
+                if (gp >= 0) dst[gp] = cmul(f, make_double2(cr - si, ci + sr));
+                if (gm >= 0) dst[gm] = cmul(f, make_double2(cr + si, ci - sr));
             }
     }
 }
@@ -467,16 +775,43 @@ int zy_pairs_per_wave(int nb2, int nb3) {
 
 const ZyLaunches& select_zy(int nb2, int nb3) {
     static const ZyLaunches table[4][4] = {
-        {zy_launches<1, 1>(), zy_launches<1, 2>(), zy_launches<1, 3>(), zy_launches<1, 4>()},
-        {zy_launches<2, 1>(), zy_launches<2, 2>(), zy_launches<2, 3>(), zy_launches<2, 4>()},
+        {{}, {}, zy_launches<1, 3>(), zy_launches<1, 4>()},  // up to 2 x 2: mtxel_fold_kernel
+        {{}, {}, zy_launches<2, 3>(), zy_launches<2, 4>()},
         {zy_launches<3, 1>(), zy_launches<3, 2>(), zy_launches<3, 3>(), zy_launches<3, 4>()},
         {zy_launches<4, 1>(), zy_launches<4, 2>(), zy_launches<4, 3>(), zy_launches<4, 4>()},
     };
     return table[nb2 - 1][nb3 - 1];
 }
 
+using FoldKernel = void (*)(const double2*, const double2*, int64_t, Rect, int, int, int, int,
+                            const double2*, const double*, const int2*, int, double2*, int, int, int);
+
+// Band pairs per wave: the sums of a pair (4 C3 of stage z, 4 C2 C3 of stage y)
+// within the registers of two waves per SIMD.
+constexpr int fold_ppw(int c2, int c3) {
+    return 4 * c3 * (c2 + 1) <= 24 ? 4 : 4 * c3 * (c2 + 1) <= 48 ? 2 : 1;
+}
+
+// Boxes of at most 16 classes on both axes are folded, half the work of the
+// unfolded stages or less.  The whole product, unfolded -> folded, 8 x 240 pairs
+// on 36^3 by classes on y and z: 12 x 4 0.41 -> 0.25 ms, 9 x 9 (40^3)
+// 0.73 -> 0.53, 16 x 9 0.74 -> 0.66, 13 x 16 0.84 -> 0.83; 4 x 4 on 20^3, 12 pairs
+// 24 -> 18 us.  Past 16 the stage-y sums of a pair no longer fit a wave's
+// registers.
+constexpr int kFoldMax = 4;  // groups of 4 classes
+
+FoldKernel select_fold(int c2, int c3) {
+#define GW_FOLD(A, B) mtxel_fold_kernel<A, B, fold_ppw(A, B)>
+#define GW_FOLD_ROW(A) {GW_FOLD(A, 1), GW_FOLD(A, 2), GW_FOLD(A, 3), GW_FOLD(A, 4)}
+    static const FoldKernel table[kFoldMax][kFoldMax] = {GW_FOLD_ROW(1), GW_FOLD_ROW(2),
+                                                         GW_FOLD_ROW(3), GW_FOLD_ROW(4)};
+#undef GW_FOLD_ROW
+#undef GW_FOLD
+    return table[c2 - 1][c3 - 1];
+}
+
 using XKernel = void (*)(const double2*, int, int, int, int, const double*, const int*, int,
-                         double, int64_t, int64_t, int, int64_t, double2*);
+                         double, int64_t, int64_t, int, int64_t, double2*, const double2*);
 
 XKernel select_x(int nb1) {
     static const XKernel table[4] = {&mtxel_x_kernel<1>, &mtxel_x_kernel<2>, &mtxel_x_kernel<3>,
@@ -545,19 +880,32 @@ std::unique_ptr<MtxelPlan> build_plan(const int n[3], const int32_t* gvec, int n
     p->n3p = ceil_div(n[2], 16) * 16;
     const int q = p->n3p / 4, nrb1 = p->n2p / 16;
     const int bw2 = p->nb2 * 16, bw3 = p->nb3 * 16, bwh3 = p->nbh3 * 16;
-    {
-        // tables, then a ring of 3 slabs (2 where 3 do not fit)
-        const int ppw = zy_pairs_per_wave(p->nbh2, p->nbh3);
-        const size_t nbands = 4 + 2 * static_cast<size_t>(ppw);
-        const size_t tables = (static_cast<size_t>(q) * p->nbh3 * 32 +
-                               static_cast<size_t>(nrb1) * 4 * p->nbh2 * 32 +
-                               static_cast<size_t>(p->nbh2) * 16 * bwh3 / 4) * sizeof(double2);
-        const size_t slab = nbands * 256 * sizeof(double2);
+    p->c2 = ceil_div(p->mh2, 4);
+    p->c3 = ceil_div(p->mh3, 4);
+    p->fold = p->c2 <= kFoldMax && p->c3 <= kFoldMax;
+    const int h2 = ceil_div(n[1], 2), h3 = ceil_div(n[2], 2);  // folded lines
+    const int nks3 = ceil_div(h3, 4), nrbf = ceil_div(h2, 8);
+    // LDS of stages z and y: tables, then a ring of 3 slabs (2 where 3 do not
+    // fit)
+    auto lds_zy = [&](size_t tables, int ppw) {
+        const size_t slab = (4 + 2 * static_cast<size_t>(ppw)) * 256 * sizeof(double2);
+        tables *= sizeof(double2);
         p->ring = tables + 3 * slab <= kMaxLds ? 3 : 2;
         p->lds_yz = tables + p->ring * slab;
-    }
+    };
+    lds_zy(static_cast<size_t>(q) * p->nbh3 * 32 + static_cast<size_t>(nrb1) * 4 * p->nbh2 * 32 +
+               static_cast<size_t>(p->nbh2) * 16 * bwh3 / 4,
+           zy_pairs_per_wave(p->nbh2, p->nbh3));
+    // one limit for all boxes; the folded tables are half as large
     if (p->lds_yz > kMaxLds)
         throw Error{-4, "grid too large for the LDS-resident twiddle operands (unsupported)"};
+    if (p->fold) {
+        lds_zy(static_cast<size_t>(nks3) * p->c3 * 16 + static_cast<size_t>(nrbf) * p->c2 * 32 +
+                   static_cast<size_t>(p->c2) * 16 * p->c3,
+               fold_ppw(p->c2, p->c3));
+        if (p->lds_yz > kMaxLds)
+            throw Error{-4, "grid too large for the LDS-resident twiddle operands (unsupported)"};
+    }
     p->n1p = ceil_div(n[0], 4) * 4;
     p->lds_x = static_cast<size_t>(p->nbh1) * (p->n1p / 4) * 64 * sizeof(double);
     if (p->lds_x > kMaxLds) throw Error{-4, "N1 too large (unsupported)"};
@@ -583,17 +931,17 @@ std::unique_ptr<MtxelPlan> build_plan(const int n[3], const int32_t* gvec, int n
         if (minus && (a == 0 || 2 * a == nn)) return -1;
         return minus ? nn - a : a;
     };
-    std::vector<int> boxf(static_cast<size_t>(p->nbh2) * 16 * bwh3, -1);
-    for (int h2 = 0; h2 < p->nbh2 * 8; ++h2)
+    std::vector<int> boxf(p->fold ? 0 : static_cast<size_t>(p->nbh2) * 16 * bwh3, -1);
+    for (int hc = 0; hc < (p->fold ? 0 : p->nbh2 * 8); ++hc)
         for (int sg = 0; sg < 2; ++sg) {
-            const int k2v = freq(lh2, h2, sg == 1, n[1]);
+            const int k2v = freq(lh2, hc, sg == 1, n[1]);
             const auto it2 = i2.find(k2v);
             if (k2v < 0 || it2 == i2.end()) continue;
             for (int col = 0; col < bwh3; ++col) {
                 const int k3v = freq(lh3, (col >> 4) * 8 + (col & 7), (col & 15) >= 8, n[2]);
                 const auto it3 = i3.find(k3v);
                 if (k3v < 0 || it3 == i3.end()) continue;
-                boxf[(static_cast<size_t>(h2) * 2 + sg) * bwh3 + col] =
+                boxf[(static_cast<size_t>(hc) * 2 + sg) * bwh3 + col] =
                     box[it2->second * bw3 + it3->second];
             }
         }
@@ -621,8 +969,72 @@ std::unique_ptr<MtxelPlan> build_plan(const int n[3], const int32_t* gvec, int n
                 }
         return w;
     };
-    const std::vector<double> w3 = real_tab(lh3, p->nbh3, q, n[2]);
-    const std::vector<double> w2 = real_tab(lh2, p->nbh2, nrb1 * 4, n[1]);
+    std::vector<double> w3, w2;
+    if (!p->fold) {
+        w3 = real_tab(lh3, p->nbh3, q, n[2]);
+        w2 = real_tab(lh2, p->nbh2, nrb1 * 4, n[1]);
+    }
+    // folded stages: cos and sin of 2 pi a u/N, u = (2 f + 1)/2 (even N) or f
+    // (odd N, the cosine of the centre f = 0 halved); zero past the line's pairs
+    // or the classes
+    auto fold_cs = [](const std::vector<int>& lh, int h, int f, int nn) {
+        if (h >= static_cast<int>(lh.size()) || f >= (nn + 1) / 2) return make_double2(0.0, 0.0);
+        const int64_t u2 = nn % 2 ? 2 * f : 2 * f + 1;  // 2 u
+        double2 r = host_root(static_cast<int64_t>(lh[h]) * u2, 2 * static_cast<int64_t>(nn));
+        if (u2 == 0) r = make_double2(0.5, 0.0);
+        return r;
+    };
+    std::vector<double2> w3f, phf;
+    std::vector<double> w2f;
+    std::vector<int2> boxf4;
+    if (p->fold) {
+        for (int ks = 0; ks < nks3; ++ks)
+            for (int g = 0; g < p->c3; ++g)
+                for (int k = 0; k < 4; ++k)
+                    for (int j = 0; j < 4; ++j) w3f.push_back(fold_cs(lh3, 4 * g + j, 4 * ks + k, n[2]));
+        // [row block][group][lane]: class 4 g + lane%4 and, in block b, pair
+        // 8 rb + 4 (b & 1) + lane/16: cosines in blocks 0 and 1, sines in 2 and 3
+        for (int rb = 0; rb < nrbf; ++rb)
+            for (int g = 0; g < p->c2; ++g)
+                for (int l = 0; l < 64; ++l) {
+                    const int b = (l >> 2) & 3;
+                    const double2 r =
+                        fold_cs(lh2, 4 * g + (l & 3), 8 * rb + 4 * (b & 1) + (l >> 4), n[1]);
+                    w2f.push_back(b < 2 ? r.x : r.y);
+                }
+        // outputs: [k2 class][sign][k3 class] -> disc of k3 = +a and -a, or -1
+        boxf4.assign(static_cast<size_t>(p->c2) * 8 * p->c3 * 4, make_int2(-1, -1));
+        phf.assign(p->n23p, make_double2(0.0, 0.0));
+        auto disc_of = [&](int k2v, int k3v) {
+            const auto a = i2.find(k2v), b = i3.find(k3v);
+            return k2v < 0 || k3v < 0 || a == i2.end() || b == i3.end()
+                       ? -1
+                       : box[a->second * bw3 + b->second];
+        };
+        // e^{2 pi i k (N - 1)/(2 N)} for the signed frequency k
+        auto centre = [](int k, int nn) {
+            return host_root(static_cast<int64_t>(k) * (nn - 1), 2 * static_cast<int64_t>(nn));
+        };
+        auto mul = [](double2 a, double2 b) {
+            return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+        };
+        for (int h2c = 0; h2c < p->mh2; ++h2c)
+            for (int sg2 = 0; sg2 < 2; ++sg2)
+                for (int h3c = 0; h3c < p->mh3; ++h3c) {
+                    int2& d = boxf4[(static_cast<size_t>(h2c) * 2 + sg2) * p->c3 * 4 + h3c];
+                    const int k2v = freq(lh2, h2c, sg2 == 1, n[1]);
+                    d.x = disc_of(k2v, freq(lh3, h3c, false, n[2]));
+                    d.y = disc_of(k2v, freq(lh3, h3c, true, n[2]));
+                    for (int sg3 = 0; sg3 < 2; ++sg3) {
+                        const int i = sg3 ? d.y : d.x;
+                        if (i < 0) continue;
+                        double2 f = mul(centre(sg2 ? -lh2[h2c] : lh2[h2c], n[1]),
+                                        centre(sg3 ? -lh3[h3c] : lh3[h3c], n[2]));
+                        if (sg2) f = make_double2(f.y, -f.x);  // the kernel leaves i times T2
+                        phf[i] = f;
+                    }
+                }
+    }
     const std::vector<double> w1 = real_tab(lh1, p->nbh1, p->n1p / 4, n[0]);
     // forward stage-x outputs: (k1 class slot, sign: 0 for k1 = a, 1 for k1 = N1 - a,
     // a != 0, N1/2) x disc index -> G index
@@ -693,6 +1105,10 @@ std::unique_ptr<MtxelPlan> build_plan(const int n[3], const int32_t* gvec, int n
     p->w3re = upload(w3);
     p->w2re = upload(w2);
     p->boxf = upload(boxf);
+    p->w3f = upload(w3f);
+    p->w2f = upload(w2f);
+    p->boxf4 = upload(boxf4);
+    p->phf = upload(phf);
     p->w1ir = upload(w1i);
     p->w2ir = upload(w2i);
     p->w3ir = upload(w3i);
@@ -707,6 +1123,10 @@ void MtxelPlan::release() {
     (void)hipFree(gmapf);
     (void)hipFree(w3re);
     (void)hipFree(boxf);
+    (void)hipFree(w3f);
+    (void)hipFree(w2f);
+    (void)hipFree(boxf4);
+    (void)hipFree(phf);
     (void)hipFree(w2re);
     (void)hipFree(w1ir);
     (void)hipFree(w2ir);
@@ -714,6 +1134,9 @@ void MtxelPlan::release() {
     (void)hipFree(boxi);
     w1re = w2re = w3re = w1ir = w2ir = w3ir = nullptr;
     gmapf = boxf = boxi = nullptr;
+    w3f = phf = nullptr;
+    w2f = nullptr;
+    boxf4 = nullptr;
     if (last_use) (void)hipEventDestroy(last_use);
     last_use = nullptr;
 }
@@ -776,13 +1199,8 @@ void launch_mtxel(const MtxelPlan& p, const double2* psi_v, const double2* psi_c
     if (ldm == 0) ldm = rc.nc;
     const int64_t npairs = static_cast<int64_t>(rc.nv) * rc.nc;
     if (npairs <= 0) return;
-    const ZyLaunches& zl = select_zy(p.nbh2, p.nbh3);
-    const int ppw = zy_pairs_per_wave(p.nbh2, p.nbh3);
-    for (int h = 0; h < zl.count; ++h)
-        GW_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(zl.k[h]),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(p.lds_yz)));
     {
+        const int ppw = p.fold ? fold_ppw(p.c2, p.c3) : zy_pairs_per_wave(p.nbh2, p.nbh3);
         // pair tiles x groups of j1 planes: enough workgroups to fill the chip
         const int gx = ceil_div(rc.nc, 2 * ppw), gy = ceil_div(rc.nv, 4);
         const int64_t tiles = static_cast<int64_t>(gx) * gy;
@@ -790,10 +1208,25 @@ void launch_mtxel(const MtxelPlan& p, const double2* psi_v, const double2* psi_c
         const int pp = ceil_div(p.n[0], want);
         const dim3 grid(gx, gy, ceil_div(p.n[0], pp));
         ProfScope ps("mtxel_zy", s);
-        for (int h = 0; h < zl.count; ++h)
-            hipLaunchKernelGGL(zl.k[h], grid, dim3(kZyThreads), p.lds_yz, s, psi_v, psi_c, p.nr, rc,
-                               p.n[0], pp, p.n[1], p.n[2], p.n2p, p.n3p, p.w3re, p.w2re, p.boxf,
-                               p.n23, t2, p.ring, zl.b2_0[h]);
+        auto prepare = [&](const void* k) {
+            GW_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           static_cast<int>(p.lds_yz)));
+        };
+        if (p.fold) {
+            const FoldKernel k = select_fold(p.c2, p.c3);
+            prepare(reinterpret_cast<const void*>(k));
+            hipLaunchKernelGGL(k, dim3(grid.x * grid.y * grid.z), dim3(kZyThreads), p.lds_yz, s,
+                               psi_v, psi_c, p.nr, rc, p.n[0], pp, p.n[1], p.n[2], p.w3f, p.w2f,
+                               p.boxf4, p.n23, t2, p.ring, gx, gy);
+        } else {
+            const ZyLaunches& zl = select_zy(p.nbh2, p.nbh3);
+            for (int h = 0; h < zl.count; ++h) {
+                prepare(reinterpret_cast<const void*>(zl.k[h]));
+                hipLaunchKernelGGL(zl.k[h], grid, dim3(kZyThreads), p.lds_yz, s, psi_v, psi_c, p.nr,
+                                   rc, p.n[0], pp, p.n[1], p.n[2], p.n2p, p.n3p, p.w3re, p.w2re,
+                                   p.boxf, p.n23, t2, p.ring, zl.b2_0[h]);
+            }
+        }
         GW_HIP_TRY(hipGetLastError());
     }
     XKernel kx = select_x(p.nbh1);
@@ -806,7 +1239,7 @@ void launch_mtxel(const MtxelPlan& p, const double2* psi_v, const double2* psi_c
         ProfScope ps("mtxel_x", s);
         hipLaunchKernelGGL(kx, dim3(static_cast<unsigned>(kb)), dim3(kThreads), p.lds_x, s,
                            t2 + k0 * static_cast<int64_t>(p.n[0]) * p.n23, p.n[0], p.n1p, p.n23,
-                           p.n23p, p.w1re, p.gmapf, p.ng, dv, kb, k0, rc.nc, ldm, m_out);
+                           p.n23p, p.w1re, p.gmapf, p.ng, dv, kb, k0, rc.nc, ldm, m_out, p.phf);
         GW_HIP_TRY(hipGetLastError());
     }
 }

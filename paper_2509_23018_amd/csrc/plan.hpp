@@ -64,6 +64,14 @@ struct MtxelPlan {
     double* w3re = nullptr;     // [n3p/4][64][nbh3]     stage-z MFMA B operand (cos | sin), lane layout
     double* w2re = nullptr;     // [n2p/4][64][nbh2]     stage-y MFMA A operand (cos | sin), lane layout
     int* boxf = nullptr;        // [nbh2*8][2][nbh3*16] (k2 class, sign, stage-y column) -> disc or -1
+    // folded stages z and y (boxes of at most 16 classes on both axes; w3re,
+    // w2re and boxf then stay null)
+    bool fold = false;
+    int c2 = 0, c3 = 0;         // groups of 4 k2, k3 classes
+    double2* w3f = nullptr;     // [ceil(h3/4)][c3][4][4] (cos, sin) of (column pair, k3 class)
+    double* w2f = nullptr;      // [ceil(h2/8)][c2][64] stage-y A operand, lane layout
+    int2* boxf4 = nullptr;      // [c2*4][2][c3*4] (k2 class, sign, k3 class) -> disc of k3 = +a, -a
+    double2* phf = nullptr;     // [n23p] phase that the folded T2 lacks
     // used by the adjoint (the transposed stages, e^{-2 pi i k j/N} as P cos + Q sin)
     int n1p16 = 0;              // N1 rounded up to 16
     double* w1ir = nullptr;     // [n1p16/16][nbh1*4][64] adjoint stage-x MFMA A operand (cos | sin)
