@@ -321,32 +321,40 @@ __global__ __launch_bounds__(256) void diag_max_kernel(const double2* __restrict
 //
 // One workgroup, so the latency of its dependent steps is the whole cost.  The
 // block lives in registers (thread (ti, tj) holds rows ti + 16 r and columns
-// tj + 16 c) and a step passes only the pivot row through LDS: its owners
-// write it as it stands, and behind the step's one barrier each wave scales it
-// for itself, an element per lane.  X is solved by one wave, a column per
-// lane, so that every lane reads the same entry of R; the order of each sum is
-// that of plain back substitution.  With the block in LDS, three barriers per
-// step and each column's rows read at a pace of its own a 64 x 64 block took
-// 107 us against 75 us.
+// tj + 16 c; blocks below the diagonal are not touched) and a step passes only
+// the pivot row through LDS: its owners write it as it stands, and behind the
+// step's one barrier each wave scales it for itself, an element per lane.  X is
+// solved by two waves, half a column entry per lane, so that every lane reads the
+// same entries of R; the order of each sum is that of plain back substitution.
+// With the block in LDS, three barriers per step and each column's rows read at
+// a pace of its own a 64 x 64 block took 107 us; with X by one wave, a column per
+// lane, and a choice between an LDS place and a zero's place (flat loads) 75 us
+// against 66 us.
 __global__ __launch_bounds__(256) void chol_block_kernel(double2* __restrict__ g, int n, int k0,
                                                          int kb, const double* __restrict__ gmax,
                                                          double2* __restrict__ x) {
     constexpr int R = kCB / 16;
     __shared__ double2 s_r[kCB][kCB + 1];
-    __shared__ double2 s_x[kCB][kCB + 1];
+    __shared__ double s_x[2][kCB][64];
+    __shared__ double s_diag[kCB];
     __shared__ double2 s_piv[2][kCB];
     __shared__ double2 s_row[4][kCB];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
     const double thr = 1e-26 * gmax[0];
     const double2 zero = make_double2(0.0, 0.0);
+    for (int e = threadIdx.x; e < 2 * kCB * 64; e += 256) (&s_x[0][0][0])[e] = 0.0;
+    for (int e = threadIdx.x; e < kCB * (kCB + 1); e += 256) (&s_r[0][0])[e] = zero;
     double2 a[R][R];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int c = 0; c < R; ++c) {
             const int i = ti + 16 * r, j = tj + 16 * c;
-            a[r][c] = i < kb && j < kb ? g[static_cast<int64_t>(k0 + i) * n + k0 + j] : zero;
+            const bool in = i < kb && j < kb;
+            const double2 v = g[in ? static_cast<int64_t>(k0 + i) * n + k0 + j
+                                   : static_cast<int64_t>(k0) * n + k0];
+            a[r][c] = make_double2(in ? v.x : 0.0, in ? v.y : 0.0);
         }
 #pragma unroll
     for (int pr = 0; pr < R; ++pr) {
@@ -366,17 +374,22 @@ __global__ __launch_bounds__(256) void chol_block_kernel(double2* __restrict__ g
                                : lane == k      ? make_double2(rk, 0.0)
                                                 : make_double2(u.x / rk, u.y / rk);
             s_row[wave][lane] = sc;
-            if (wave == 0) s_r[k][lane] = sc;
+            if (wave == 0) s_r[k][lane] = make_double2(lane == k ? 0.0 : sc.x, sc.y);
+            if (wave == 0 && lane == k) s_diag[k] = sc.x;
             __builtin_amdgcn_wave_barrier();
-            // trailing rows: a[i][j] -= conj(r[k][i]) r[k][j], i > k
+            // trailing rows: a[i][j] -= conj(r[k][i]) r[k][j], i > k, the upper
+            // 16 x 16 blocks
             double2 rj[R];
 #pragma unroll
-            for (int c = 0; c < R; ++c) rj[c] = s_row[wave][tj + 16 * c];
+            for (int c = pr; c < R; ++c) rj[c] = s_row[wave][tj + 16 * c];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double2 p = ti + 16 * r > k ? s_row[wave][ti + 16 * r] : zero;
+            for (int r = pr; r < R; ++r) {
+                double2 p = s_row[wave][ti + 16 * r];  // a choice of values, not of places
+                const bool below = ti + 16 * r > k;
+                p.x = below ? p.x : 0.0;
+                p.y = below ? p.y : 0.0;
 #pragma unroll
-                for (int c = 0; c < R; ++c) {
+                for (int c = r; c < R; ++c) {
                     a[r][c].x -= p.x * rj[c].x + p.y * rj[c].y;  // conj(p) r
                     a[r][c].y -= p.x * rj[c].y - p.y * rj[c].x;
                 }
@@ -384,30 +397,47 @@ __global__ __launch_bounds__(256) void chol_block_kernel(double2* __restrict__ g
         }
     }
     __syncthreads();
-    // X = R^-1, column j by lane j: back substitution upwards (columns past j
-    // of a row of R meet zeros of X)
-    if (wave == 0) {
-        const int j = lane;
-        for (int i = 0; i < kb; ++i) s_x[i][j] = zero;
-        for (int i = kb - 1; i >= 0; --i) {
-            const double rii = s_r[i][i].x;
-            double sr = 0.0, si = 0.0;
-#pragma unroll 8
-            for (int k = i + 1; k < kb; ++k) {
-                const double2 p = s_r[i][k], q = s_x[k][j];
-                sr += p.x * q.x - p.y * q.y;
-                si += p.x * q.y + p.y * q.x;
+    // X = R^-1 by back substitution upwards: column j = 32 wave + lane/2, its real
+    // part in the even lane and its imaginary part in the odd one: Re p x =
+    // fma(p.x, x.x, p.y (-x.y)), Im p x = fma(p.y, x.x, p.x x.y).  The sum of row i
+    // runs upwards from k = i + 1, by whole groups of 8: the k before it meet
+    // zeros of R (s_r has no diagonal), those past kb zeros of X.
+    if (wave < 2) {
+        const int j = 32 * wave + (lane >> 1);
+        const bool im = lane & 1;
+        double* xl = &s_x[wave][0][lane];
+        const double2* xj = reinterpret_cast<const double2*>(&s_x[wave][0][lane & ~1]);
+        const double* pr = reinterpret_cast<const double*>(&s_r[0][0]) + im;
+        const double* pi = reinterpret_cast<const double*>(&s_r[0][0]) + !im;
+        const long long sign = im ? 0 : 1ll << 63;
+#pragma unroll
+        for (int ib = kCB / 8 - 1; ib >= 0; --ib) {
+#pragma unroll 1
+            for (int ii = 7; ii >= 0; --ii) {
+                const int i = 8 * ib + ii;
+                if (i >= kb || i >= 32 * (wave + 1)) continue;  // uniform; X[i][j] = 0
+                double sum = 0.0;
+#pragma unroll
+                for (int k = 8 * ib; k < kCB; ++k) {
+                    const int e = 2 * (i * (kCB + 1) + k);
+                    const double2 q = xj[32 * k];
+                    const double qi = __longlong_as_double(__double_as_longlong(q.y) ^ sign);
+                    sum += fma(pr[e], q.x, pi[e] * qi);
+                }
+                const double rii = s_diag[i];
+                double v = 0.0;
+                if (rii > 0.0 && i <= j && j < kb)
+                    v = i == j ? (im ? 0.0 : 1.0 / rii) : -sum / rii;
+                xl[64 * i] = v;
             }
-            if (rii > 0.0 && i <= j && j < kb)
-                s_x[i][j] = i == j ? make_double2(1.0 / rii, 0.0)
-                                   : make_double2(-sr / rii, -si / rii);
         }
     }
     __syncthreads();
     for (int e = threadIdx.x; e < kb * kb; e += 256) {
         const int i = e / kb, j = e % kb;
-        g[static_cast<int64_t>(k0 + i) * n + k0 + j] = s_r[i][j];
-        x[i * kCB + j] = s_x[i][j];
+        g[static_cast<int64_t>(k0 + i) * n + k0 + j] =
+            i == j ? make_double2(s_diag[i], 0.0) : s_r[i][j];
+        x[i * kCB + j] = *reinterpret_cast<const double2*>(&s_x[j >> 5][i][2 * (j & 31)]);
     }
 }
 
