@@ -48,6 +48,16 @@ __global__ __launch_bounds__(256) void build_eps_kernel(const double2* __restric
 // Matrices below are row-major n x n with leading dimension n, matrix w of the
 // batch at a + w * sa.
 
+__device__ __forceinline__ double2 crecip(double2 a) {  // 1 / a
+    const double den = a.x * a.x + a.y * a.y;
+    return make_double2(a.x / den, -a.y / den);
+}
+// a - b c, a rounded once (as a chain of FMAs onto a it would be twice)
+__device__ __forceinline__ double2 csub_mul(double2 a, double2 b, double2 c) {
+    const double2 v = cmul(b, c);
+    return make_double2(a.x - v.x, a.y - v.y);
+}
+
 // Workgroup 0 of matrix w: d[w] = A[w][K,K]^-1 for the bk x bk block at
 // (k0, k0) (bk <= 64), scalar Gauss-Jordan without pivoting; d[w] at d +
 // w * kB * kB, leading dimension kB.  The others: L[w] = A[w][:, K] (rows in K
@@ -56,17 +66,21 @@ __global__ __launch_bounds__(256) void build_eps_kernel(const double2* __restric
 //
 // The inverse is a chain of bk dependent steps on one workgroup, so the latency
 // of a step is the whole cost.  The block lives in registers (thread (ti, tj)
-// holds rows ti + 16 r and columns tj + 16 c); a step passes only the pivot row
-// and column through LDS, in two buffers, so it costs one barrier, one round of
-// LDS reads and one division.  Holding the block in LDS took four barriers and
-// three passes over it per step: 182 us for a 64 x 64 block against 42 us.
-// Two or four threads per 2 x 4 or 2 x 2 entries (47 and 50 us), and forming
-// only the next pivot's row and column before the barrier (42 us), did not help.
+// holds rows ti + 16 r and columns tj + 16 c).  Two steps go together: the two
+// pivot rows and columns pass through LDS as they stand, in two buffers, and
+// every thread takes its own part of the second row and column through the first
+// step itself, so that two steps cost one barrier and one round of LDS reads.
+// A launch with a 64 x 64 block: 182 us with the block in LDS (four barriers and
+// three passes over it per step), 44 us by single steps, 39 us by two.  35 us
+// with FMAs straight onto the entry, which rounds it twice per step: the
+// inverse's error grows by 10 to 70 %, not kept.  Two or four threads per 2 x 4
+// or 2 x 2 entries, and forming only the next pivot's row and column before the
+// barrier, did not help.
 __global__ __launch_bounds__(256) void pivot_kernel(double2* __restrict__ a, int n, int64_t sa,
                                                     int k0, int bk, double2* __restrict__ d,
                                                     double2* __restrict__ l) {
     constexpr int R = kB / 16;
-    __shared__ double2 s_row[2][kB], s_col[2][kB];
+    __shared__ double2 s_row[2][2][kB], s_col[2][2][kB];  // [buffer][step]
     const int64_t w = blockIdx.y;
     double2* aw = a + w * sa;
     if (blockIdx.x > 0) {
@@ -87,46 +101,63 @@ __global__ __launch_bounds__(256) void pivot_kernel(double2* __restrict__ a, int
 #pragma unroll
         for (int c = 0; c < R; ++c) {
             const int i = ti + 16 * r, j = tj + 16 * c;
-            x[r][c] = i < bk && j < bk ? aw[static_cast<int64_t>(k0 + i) * n + k0 + j]
-                                       : make_double2(0.0, 0.0);
+            const bool in = i < bk && j < bk;
+            const double2 v = aw[in ? static_cast<int64_t>(k0 + i) * n + k0 + j
+                                    : static_cast<int64_t>(k0) * n + k0];
+            // past the block the identity: the second step of an odd bk
+            x[r][c] = make_double2(in ? v.x : i == j ? 1.0 : 0.0, in ? v.y : 0.0);
         }
 #pragma unroll
     for (int pr = 0; pr < R; ++pr) {
-        for (int pt = 0; pt < 16; ++pt) {
-            const int p = 16 * pr + pt, buf = p & 1;
+#pragma unroll 1
+        for (int pt = 0; pt < 16; pt += 2) {
+            const int p = 16 * pr + pt, buf = (pt >> 1) & 1;
             if (p >= bk) break;
-            if (tj == pt)
+            if ((tj & ~1) == pt)
 #pragma unroll
-                for (int r = 0; r < R; ++r) s_col[buf][ti + 16 * r] = x[r][pr];
-            if (ti == pt)
+                for (int r = 0; r < R; ++r) s_col[buf][tj & 1][ti + 16 * r] = x[r][pr];
+            if ((ti & ~1) == pt)
 #pragma unroll
-                for (int c = 0; c < R; ++c) s_row[buf][tj + 16 * c] = x[pr][c];
+                for (int c = 0; c < R; ++c) s_row[buf][ti & 1][tj + 16 * c] = x[pr][c];
             __syncthreads();
-            const double2 piv = s_row[buf][p];
-            const double den = piv.x * piv.x + piv.y * piv.y;
-            const double2 inv = make_double2(piv.x / den, -piv.y / den);
-            // row p scaled, its pivot 1 / pivot; a_ij -= a_ip a_pj for the other
-            // rows (column p: 0 - a_ip / pivot)
-            double2 row[R];
+            // a step: row p scaled, its pivot 1 / pivot; a_ij -= a_ip a_pj for the
+            // other rows (column p: 0 - a_ip / pivot).  r1, r2: the scaled rows.
+            const double2 inv1 = crecip(s_row[buf][0][p]);
+            const double2 f = s_row[buf][1][p];  // a_{p+1,p}
+            const double2 h = cmul(inv1, s_row[buf][0][p + 1]);  // r1 in column p + 1
+            const double2 inv2 = crecip(csub_mul(s_row[buf][1][p + 1], f, h));
+            double2 r1[R], r2[R];
 #pragma unroll
-            for (int c = 0; c < R; ++c) row[c] = cmul(inv, s_row[buf][tj + 16 * c]);
+            for (int c = 0; c < R; ++c) {
+                const int j = tj + 16 * c;
+                r1[c] = cmul(inv1, s_row[buf][0][j]);
+                r2[c] = s_row[buf][1][j];
+            }
             if (tj == pt) {
-                row[pr] = inv;
+                r1[pr] = inv1;
+                r2[pr] = make_double2(0.0, 0.0);
+            }
+#pragma unroll
+            for (int c = 0; c < R; ++c) r2[c] = cmul(inv2, csub_mul(r2[c], f, r1[c]));
+            if (tj == pt + 1) {
+                r1[pr] = make_double2(0.0, 0.0);
+                r2[pr] = inv2;
+            }
+            if ((tj & ~1) == pt)  // columns p and p + 1 start from zero
 #pragma unroll
                 for (int r = 0; r < R; ++r) x[r][pr] = make_double2(0.0, 0.0);
-            }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const double2 col = s_col[buf][ti + 16 * r];
+                const double2 c1 = s_col[buf][0][ti + 16 * r];
+                const double2 c2 = csub_mul(s_col[buf][1][ti + 16 * r], c1, h);
 #pragma unroll
-                for (int c = 0; c < R; ++c) {
-                    const double2 v = cmul(col, row[c]);
-                    x[r][c] = make_double2(x[r][c].x - v.x, x[r][c].y - v.y);
-                }
+                for (int c = 0; c < R; ++c)
+                    x[r][c] = csub_mul(csub_mul(x[r][c], c1, r1[c]), c2, r2[c]);
             }
-            if (ti == pt)
+            if ((ti & ~1) == pt)
 #pragma unroll
-                for (int c = 0; c < R; ++c) x[pr][c] = row[c];
+                for (int c = 0; c < R; ++c)
+                    x[pr][c] = ti == pt ? csub_mul(r1[c], h, r2[c]) : r2[c];
         }
     }
 #pragma unroll
@@ -144,7 +175,8 @@ __global__ __launch_bounds__(256) void pivot_kernel(double2* __restrict__ a, int
 // complex one.  Both operands fit LDS whole, so it is one load, one barrier
 // and 16 k-steps; the columns are read before they are overwritten.  On the
 // chain of an inverse, where each launch costs its latency (64 of these for
-// 2,007 G): 9 us at n = 512 against 5 + 5 us as a GEMM and a copy.
+// 2,007 G): 9 us at n = 512 against 5 + 5 us as a GEMM and a copy; 7 us with
+// the choices past the edges made between values (no flat loads).
 __global__ __launch_bounds__(256) void pivot_rows_kernel(double2* __restrict__ a, int n, int64_t sa,
                                                          int k0, int bk,
                                                          const double2* __restrict__ d,
@@ -154,17 +186,20 @@ __global__ __launch_bounds__(256) void pivot_rows_kernel(double2* __restrict__ a
     const int64_t w = blockIdx.y;
     const int j0 = blockIdx.x * 16;
     double2* aw = a + w * sa + static_cast<int64_t>(k0) * n;
-    const double2 zero = make_double2(0.0, 0.0);
     double2 vd[16], va[4];  // every load in flight before the first is used
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int e = threadIdx.x + 256 * u, k = e / 16, j = j0 + e % 16;
-        va[u] = k < bk && j < n ? aw[static_cast<int64_t>(k) * n + j] : zero;
+        const bool in = k < bk && j < n;
+        const double2 v = aw[in ? static_cast<int64_t>(k) * n + j : 0];
+        va[u] = make_double2(in ? v.x : 0.0, in ? v.y : 0.0);
     }
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int e = threadIdx.x + 256 * u, i = e / kB, k = e % kB;
-        vd[u] = i < bk && k < bk ? d[w * kB * kB + e] : zero;
+        const bool in = i < bk && k < bk;
+        const double2 v = d[w * kB * kB + (in ? e : 0)];
+        vd[u] = make_double2(in ? v.x : 0.0, in ? v.y : 0.0);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
