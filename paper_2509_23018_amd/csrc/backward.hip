@@ -47,6 +47,154 @@ __global__ __launch_bounds__(256) void ddelta_kernel(const double* __restrict__ 
     }
 }
 
+// The sums of P1 = M W of bwd_gm_kernel's tile (rows k0.., columns i0..) for one
+// product (SYM), in the order of its own loop.  Two LDS buffers: stage t + 2 is
+// loaded into registers while stage t is multiplied and written to LDS a stage
+// before its use, one barrier per stage, and every instruction between the
+// MFMAs is placed (one load per two MFMAs from the start of the stage, one LDS
+// write per MFMA at its end, the next k-step's fragments and sums before the
+// current one ends).  Rows and columns past the edge are clamped: they feed
+// only entries that are not stored; the last, partial stage masks its k.
+// Bound by the FP64 matrix pipe; 3,840 pairs x 1,189 G beside the next chunk's
+// transforms: 710 us with one LDS buffer and the loads in a run before the MFMAs,
+// 603 us so (54 TFLOP/s of the flops executed).  TM = 64: the same.
+template <int TM>
+__device__ __forceinline__ void gm_sym_product(const double2* __restrict__ m, int64_t kc, int ng,
+                                               const double2* __restrict__ w, int64_t k0, int i0,
+                                               double2 (&s_a)[2][TM][17],
+                                               double2 (&s_b)[2][16][64],
+                                               dbl4 (&p1)[TM / 32][2], dbl4 (&p2)[TM / 32][2],
+                                               dbl4 (&p3)[TM / 32][2]) {
+    constexpr int BX = TM / 32, KT = 16, PD = 2, NA = TM * KT / 256, NB = 64 * KT / 256;
+    constexpr int NE = NA + NB, NM = 6 * BX, NQ = KT / 4;
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63, row = lane & 15, kq = lane >> 4;
+    const int wi = wave >> 1, wj = wave & 1;
+    // staged element e = tid + 256 u: row e / 16 of M and k e % 16; k e / 64 and
+    // column e % 64 of W
+    const double2 *pa[NA], *pb[NB];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+        const int e = tid + 256 * u;
+        pa[u] = m + std::min<int64_t>(k0 + (e >> 4), kc - 1) * ng + (e & 15);
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const int e = tid + 256 * u;
+        pb[u] = w + static_cast<int64_t>(e >> 6) * ng + std::min(i0 + (e & 63), ng - 1);
+    }
+    double2 ra[PD][NA], rb[PD][NB];
+    // component loads: a whole-struct copy would be fused with the LDS write
+    // into one copy behind the MFMAs
+    auto load = [&](int slot, int e) {
+        if (e < NA) {
+            ra[slot][e].x = pa[e]->x;
+            ra[slot][e].y = pa[e]->y;
+            pa[e] += KT;
+        } else {
+            rb[slot][e - NA].x = pb[e - NA]->x;
+            rb[slot][e - NA].y = pb[e - NA]->y;
+            pb[e - NA] += static_cast<int64_t>(KT) * ng;
+        }
+    };
+    const int nfull = ng / KT, rem = ng % KT, nst = nfull + (rem > 0);
+    auto fetch = [&](int st, int slot) {
+        if (st < nfull) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) load(slot, e);
+        } else if (st < nst) {  // the last, partial stage: k past the end is zero
+#pragma unroll
+            for (int u = 0; u < NA; ++u)
+                ra[slot][u] = (tid & 15) < rem ? *pa[u] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                rb[slot][u] = ((tid + 256 * u) >> 6) < rem ? *pb[u] : make_double2(0.0, 0.0);
+        }
+    };
+    auto store1 = [&](int slot, int buf, int e) {
+        const int t = tid + 256 * (e < NA ? e : e - NA);
+        if (e < NA)
+            s_a[buf][t >> 4][t & 15] = make_double2(ra[slot][e].x, ra[slot][e].y);
+        else
+            s_b[buf][t >> 6][t & 63] = make_double2(rb[slot][e - NA].x, rb[slot][e - NA].y);
+    };
+    auto store = [&](int slot, int buf) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) store1(slot, buf, e);
+    };
+    auto read = [&](int buf, int q, double2 (&a)[BX], double2 (&b)[2]) {
+#pragma unroll
+        for (int x = 0; x < BX; ++x) a[x] = s_a[buf][wi * (TM / 2) + x * 16 + row][q * 4 + kq];
+#pragma unroll
+        for (int y = 0; y < 2; ++y) b[y] = s_b[buf][q * 4 + kq][wj * 32 + y * 16 + row];
+    };
+    auto sums = [&](const double2 (&a)[BX], const double2 (&b)[2], double (&as)[BX],
+                    double (&bs)[2]) {
+#pragma unroll
+        for (int x = 0; x < BX; ++x) as[x] = a[x].x + a[x].y;
+#pragma unroll
+        for (int y = 0; y < 2; ++y) bs[y] = b[y].x + b[y].y;
+    };
+    auto mfma1 = [&](int i, const double2 (&a)[BX], const double2 (&b)[2], const double (&as)[BX],
+                     const double (&bs)[2]) {
+        const int x = i / 6, y = i / 3 % 2;
+        if (i % 3 == 0) p1[x][y] = mfma_f64(a[x].x, b[y].x, p1[x][y]);
+        if (i % 3 == 1) p2[x][y] = mfma_f64(a[x].y, b[y].y, p2[x][y]);
+        if (i % 3 == 2) p3[x][y] = mfma_f64(as[x], bs[y], p3[x][y]);
+    };
+    fetch(0, 0);
+    store(0, 0);
+    __syncthreads();
+    fetch(1, 1);
+    int st = 0;
+    for (; st + 3 < nfull; st += PD) {
+#pragma unroll
+        for (int d = 0; d < PD; ++d) {
+            double2 a[2][BX], b[2][2];
+            double as[2][BX], bs[2][2];
+            read(d, 0, a[0], b[0]);
+            sums(a[0], b[0], as[0], bs[0]);
+            __builtin_amdgcn_s_setprio(2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int f = q & 1;
+#pragma unroll
+                for (int i = 0; i < NM; ++i) {
+                    mfma1(i, a[f], b[f], as[f], bs[f]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int t = q * NM + i, e = t - (NQ * NM - NE - 1);
+                    if (t % 2 == 1 && t / 2 < NE) load(d, t / 2);
+                    if (e >= 0 && e < NE) store1(d ^ 1, d ^ 1, e);
+                    if (i == (NM - 2) / 2 && q + 1 < NQ) read(d, q + 1, a[f ^ 1], b[f ^ 1]);
+                    if (i == NM - 2 && q + 1 < NQ) sums(a[f ^ 1], b[f ^ 1], as[f ^ 1], bs[f ^ 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_s_setprio(0);
+            __syncthreads();
+        }
+    }
+    for (; st < nst; st += PD) {
+#pragma unroll
+        for (int d = 0; d < PD; ++d) {
+            if (st + d >= nst) break;
+            fetch(st + d + PD, d);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                double2 a[BX], b[2];
+                double as[BX], bs[2];
+                read(d, q, a, b);
+                sums(a, b, as, bs);
+#pragma unroll
+                for (int i = 0; i < NM; ++i) mfma1(i, a, b, as, bs);
+            }
+            if (st + d + 1 < nst) store(d ^ 1, d ^ 1);
+            __syncthreads();
+        }
+    }
+}
+
 // P1 = M W and P2 = M W^H for one TM (pairs) x 64 (G) tile; fused epilogue.
 // 4 waves of (TM/2) x 32.  TM = 32 cuts the last partial round of a launch
 // to half of what 64 x 64 tiles leave.
@@ -67,9 +215,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
                                                      double2* __restrict__ gm,
                                                      double2* __restrict__ qpart, int mode) {
     constexpr int BX = TM / 32, NA = TM * 16 / 256;
-    __shared__ double2 s_a[TM][17];
-    __shared__ double2 s_b1[16][64];
-    __shared__ double2 s_b2[16][64];
+    constexpr int NBUF = SYM ? 2 : 1;
+    __shared__ double2 s_a2[NBUF][TM][17];
+    __shared__ double2 s_b[2][16][64];  // SYM: of two stages; else W and W^H
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, row = lane & 15, kq = lane >> 4;
     const int wi = wave >> 1, wj = wave & 1;
@@ -84,98 +232,101 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
         for (int y = 0; y < 2; ++y)
             p1r[x][y] = p1i[x][y] = p1s[x][y] = p2r[x][y] = p2i[x][y] = p2s[x][y] = zero4();
 
-    // Stage j0 (16 G) of the three operands: fetched into registers one stage
-    // ahead, so that the global loads of stage j0 + 16 run under the MFMAs of
-    // stage j0.  The loads are unconditional (addresses clamped into the
-    // arrays) and nothing uses a loaded value before the stage is written to
-    // LDS: the bounds masks and the conjugation of the W^H operand are applied
-    // there, after the MFMAs, so no wait on a load lands before them.
-    double2 ra[NA], rb1[4], rb2[4];
-    const int64_t klast = kc - 1;
-    const int glast = ng - 1;
-    auto fetch = [&](int j0) {
+    if constexpr (SYM) {
+        gm_sym_product<TM>(m, kc, ng, w, k0, i0, s_a2, s_b, p1r, p1i, p1s);
+    } else {
+        auto& s_a = s_a2[0];
+        auto& s_b1 = s_b[0];
+        auto& s_b2 = s_b[1];
+        // Stage j0 (16 G) of the three operands: fetched into registers one stage
+        // ahead, so that the global loads of stage j0 + 16 run under the MFMAs of
+        // stage j0.  The loads are unconditional (addresses clamped into the
+        // arrays) and nothing uses a loaded value before the stage is written to
+        // LDS: the bounds masks and the conjugation of the W^H operand are applied
+        // there, after the MFMAs, so no wait on a load lands before them.
+        double2 ra[NA], rb1[4], rb2[4];
+        const int64_t klast = kc - 1;
+        const int glast = ng - 1;
+        auto fetch = [&](int j0) {
 #pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            const int e = tid + 256 * u;
-            const int64_t k = std::min<int64_t>(k0 + (e >> 4), klast);
-            const double2* src = m + k * ng + std::min(j0 + (e & 15), glast);
-            ra[u].x = src->x;  // component loads (a struct copy into LDS may be
-            ra[u].y = src->y;  // fused into one copy issued after the MFMAs)
-        }
+            for (int u = 0; u < NA; ++u) {
+                const int e = tid + 256 * u;
+                const int64_t k = std::min<int64_t>(k0 + (e >> 4), klast);
+                const double2* src = m + k * ng + std::min(j0 + (e & 15), glast);
+                ra[u].x = src->x;  // component loads (a struct copy into LDS may be
+                ra[u].y = src->y;  // fused into one copy issued after the MFMAs)
+            }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = tid + 256 * u;
-            const double2* s1 = w + static_cast<int64_t>(std::min(j0 + (e >> 6), glast)) * ng +
-                                std::min(i0 + (e & 63), glast);
-            const double2* s2 = w + static_cast<int64_t>(std::min(i0 + (e >> 4), glast)) * ng +
-                                std::min(j0 + (e & 15), glast);
-            rb1[u].x = s1->x;
-            rb1[u].y = s1->y;
-            if (!SYM) {
+            for (int u = 0; u < 4; ++u) {
+                const int e = tid + 256 * u;
+                const double2* s1 = w + static_cast<int64_t>(std::min(j0 + (e >> 6), glast)) * ng +
+                                    std::min(i0 + (e & 63), glast);
+                const double2* s2 = w + static_cast<int64_t>(std::min(i0 + (e >> 4), glast)) * ng +
+                                    std::min(j0 + (e & 15), glast);
+                rb1[u].x = s1->x;
+                rb1[u].y = s1->y;
                 rb2[u].x = s2->x;
                 rb2[u].y = s2->y;
             }
-        }
-    };
-    const double2 zero = make_double2(0.0, 0.0);
-    fetch(0);
-    for (int j0 = 0; j0 < ng; j0 += 16) {
-        __syncthreads();  // every wave is done with the previous stage
+        };
+        const double2 zero = make_double2(0.0, 0.0);
+        fetch(0);
+        for (int j0 = 0; j0 < ng; j0 += 16) {
+            __syncthreads();  // every wave is done with the previous stage
 #pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            const int e = tid + 256 * u;
-            const bool ok = k0 + (e >> 4) < kc && j0 + (e & 15) < ng;
-            s_a[e >> 4][e & 15] = ok ? make_double2(ra[u].x, ra[u].y) : zero;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = tid + 256 * u;
-            const bool ok1 = j0 + (e >> 6) < ng && i0 + (e & 63) < ng;
-            const bool ok2 = i0 + (e >> 4) < ng && j0 + (e & 15) < ng;
-            s_b1[e >> 6][e & 63] = ok1 ? make_double2(rb1[u].x, rb1[u].y) : zero;
-            if (!SYM) s_b2[e & 15][e >> 4] = ok2 ? make_double2(rb2[u].x, -rb2[u].y) : zero;
-        }
-        __syncthreads();
-        // issue priority 1 for the loads, 2 over the MFMAs, 0 for the stores
-        // and barriers: the wave with MFMAs to issue goes first on the SIMD
-        __builtin_amdgcn_s_setprio(1);
-        if (j0 + 16 < ng) fetch(j0 + 16);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            double2 a[BX], b1[2], b2[2];
-#pragma unroll
-            for (int x = 0; x < BX; ++x) a[x] = s_a[wi * (TM / 2) + x * 16 + row][s * 4 + kq];
-#pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                b1[y] = s_b1[s * 4 + kq][wj * 32 + y * 16 + row];
-                if (!SYM) b2[y] = s_b2[s * 4 + kq][wj * 32 + y * 16 + row];
-            }
-            double as[BX], bs1[2], bs2[2];
-#pragma unroll
-            for (int x = 0; x < BX; ++x) as[x] = a[x].x + a[x].y;
-#pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                bs1[y] = b1[y].x + b1[y].y;
-                if (!SYM) bs2[y] = b2[y].x + b2[y].y;
+            for (int u = 0; u < NA; ++u) {
+                const int e = tid + 256 * u;
+                const bool ok = k0 + (e >> 4) < kc && j0 + (e & 15) < ng;
+                s_a[e >> 4][e & 15] = ok ? make_double2(ra[u].x, ra[u].y) : zero;
             }
 #pragma unroll
-            for (int x = 0; x < BX; ++x)
+            for (int u = 0; u < 4; ++u) {
+                const int e = tid + 256 * u;
+                const bool ok1 = j0 + (e >> 6) < ng && i0 + (e & 63) < ng;
+                const bool ok2 = i0 + (e >> 4) < ng && j0 + (e & 15) < ng;
+                s_b1[e >> 6][e & 63] = ok1 ? make_double2(rb1[u].x, rb1[u].y) : zero;
+                s_b2[e & 15][e >> 4] = ok2 ? make_double2(rb2[u].x, -rb2[u].y) : zero;
+            }
+            __syncthreads();
+            // issue priority 1 for the loads, 2 over the MFMAs, 0 for the stores
+            // and barriers: the wave with MFMAs to issue goes first on the SIMD
+            __builtin_amdgcn_s_setprio(1);
+            if (j0 + 16 < ng) fetch(j0 + 16);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double2 a[BX], b1[2], b2[2];
+#pragma unroll
+                for (int x = 0; x < BX; ++x) a[x] = s_a[wi * (TM / 2) + x * 16 + row][s * 4 + kq];
 #pragma unroll
                 for (int y = 0; y < 2; ++y) {
-                    p1r[x][y] = mfma_f64(a[x].x, b1[y].x, p1r[x][y]);
-                    p1i[x][y] = mfma_f64(a[x].y, b1[y].y, p1i[x][y]);
-                    p1s[x][y] = mfma_f64(as[x], bs1[y], p1s[x][y]);
-                    if (!SYM) {
+                    b1[y] = s_b1[s * 4 + kq][wj * 32 + y * 16 + row];
+                    b2[y] = s_b2[s * 4 + kq][wj * 32 + y * 16 + row];
+                }
+                double as[BX], bs1[2], bs2[2];
+#pragma unroll
+                for (int x = 0; x < BX; ++x) as[x] = a[x].x + a[x].y;
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    bs1[y] = b1[y].x + b1[y].y;
+                    bs2[y] = b2[y].x + b2[y].y;
+                }
+#pragma unroll
+                for (int x = 0; x < BX; ++x)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        p1r[x][y] = mfma_f64(a[x].x, b1[y].x, p1r[x][y]);
+                        p1i[x][y] = mfma_f64(a[x].y, b1[y].y, p1i[x][y]);
+                        p1s[x][y] = mfma_f64(as[x], bs1[y], p1s[x][y]);
                         p2r[x][y] = mfma_f64(a[x].x, b2[y].x, p2r[x][y]);
                         p2i[x][y] = mfma_f64(a[x].y, b2[y].y, p2i[x][y]);
                         p2s[x][y] = mfma_f64(as[x], bs2[y], p2s[x][y]);
                     }
-                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
     }
 
 #pragma unroll
