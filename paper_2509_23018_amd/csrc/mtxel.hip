@@ -37,11 +37,13 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int64_t kMaxGrid = int64_t(1) << 30;  // pairs per launch
 
 double2 host_root(int64_t num, int64_t den) {
-    // e^{+2 pi i num/den} with the argument reduced to [0, den)
+    // e^{+2 pi i num/den} with the argument reduced to [0, den), in long double:
+    // rounding the angle to double alone puts up to 4e-16 into a root
     int64_t r = num % den;
     if (r < 0) r += den;
-    const double a = 2.0 * M_PI * static_cast<double>(r) / static_cast<double>(den);
-    return make_double2(std::cos(a), std::sin(a));
+    const long double a = 2.0L * std::acos(-1.0L) * static_cast<long double>(r) /
+                          static_cast<long double>(den);
+    return make_double2(static_cast<double>(std::cos(a)), static_cast<double>(std::sin(a)));
 }
 
 template <typename T>
@@ -1011,13 +1013,6 @@ std::unique_ptr<MtxelPlan> build_plan(const int n[3], const int32_t* gvec, int n
                        ? -1
                        : box[a->second * bw3 + b->second];
         };
-        // e^{2 pi i k (N - 1)/(2 N)} for the signed frequency k
-        auto centre = [](int k, int nn) {
-            return host_root(static_cast<int64_t>(k) * (nn - 1), 2 * static_cast<int64_t>(nn));
-        };
-        auto mul = [](double2 a, double2 b) {
-            return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-        };
         for (int h2c = 0; h2c < p->mh2; ++h2c)
             for (int sg2 = 0; sg2 < 2; ++sg2)
                 for (int h3c = 0; h3c < p->mh3; ++h3c) {
@@ -1028,8 +1023,11 @@ std::unique_ptr<MtxelPlan> build_plan(const int n[3], const int32_t* gvec, int n
                     for (int sg3 = 0; sg3 < 2; ++sg3) {
                         const int i = sg3 ? d.y : d.x;
                         if (i < 0) continue;
-                        double2 f = mul(centre(sg2 ? -lh2[h2c] : lh2[h2c], n[1]),
-                                        centre(sg3 ? -lh3[h3c] : lh3[h3c], n[2]));
+                        // e^{2 pi i (k2 (N2 - 1)/(2 N2) + k3 (N3 - 1)/(2 N3))}, signed k
+                        const int64_t k2 = sg2 ? -lh2[h2c] : lh2[h2c];
+                        const int64_t k3 = sg3 ? -lh3[h3c] : lh3[h3c];
+                        double2 f = host_root(k2 * (n[1] - 1) * n[2] + k3 * (n[2] - 1) * n[1],
+                                              2 * static_cast<int64_t>(n[1]) * n[2]);
                         if (sg2) f = make_double2(f.y, -f.x);  // the kernel leaves i times T2
                         phf[i] = f;
                     }
